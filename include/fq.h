@@ -146,8 +146,8 @@ size_t fq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int bits);
  *   ws        scratch of at least fq_gemm_workspace_bytes(M, N, K, bits) bytes (0 when
  *             the shape needs none; ws may then be NULL).  It needs no initialization;
  *             it holds the INT32 partial sums of a split K between the GEMM kernel and
- *             its epilogue, or (W4A4, a few hundred rows at long K) a k-step-major copy
- *             of a_codes that the GEMM reads with coalesced loads.  Calls that share a
+ *             its epilogue, or (W4A4, a few hundred rows at long K) a rearranged copy of
+ *             a_codes that the GEMM reads with coalesced loads.  Calls that share a
  *             workspace race unless they are ordered, e.g. on one stream.
  * Accumulation is exact: |acc| <= K q^2 < 2^31 for K <= 32768 at INT4 and
  * K <= 32768 at INT8 (127^2 * 32768 < 2^31 holds up to K = 133152). */
@@ -180,8 +180,8 @@ fq_status fq_gemm_w4a16(const void *x_bf16, int64_t ldx, const void *w_packed, c
 
 /* Workspace bytes fq_linear needs: the intermediate activation codes and scales, and the
  * split-K partial sums.  Scratch with no initialization requirement.  (The intermediate
- * codes are the canonical nibbles or int8, or for the shapes the k-group GEMM serves the
- * same nibbles stored k-step major: the same bytes in another order.) */
+ * codes are the canonical nibbles or int8, or for the shapes whose GEMM reads them so the
+ * same codes k major: as many bytes, arranged for that kernel's loads.) */
 size_t fq_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, int bits);
 
 /* The whole runtime projection for one consumer (Alg. 1 runtime; eqs. (5), (8)):

@@ -22,7 +22,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfq.so")
-SOURCES = ["fq_api.cpp", "fq_quant.hip", "fq_rotate.hip", "fq_gemm.hip", "fq_gemm_kg.hip", "fq_gptq.hip",
+SOURCES = ["fq_api.cpp", "fq_quant.hip", "fq_rotate.hip", "fq_gemm.hip", "fq_gemm_kg.hip", "fq_gemm_wide.hip", "fq_gptq.hip",
            "fq_small.hip"]
 ARCH = "gfx950"
 

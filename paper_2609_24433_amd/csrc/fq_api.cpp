@@ -156,8 +156,7 @@ fq_status check_gemm(const void *a, const float *delta, const void *w, const flo
 fq_status gemm_common(const void *a_codes, int a_fmt, int64_t lda, const float *delta,
                       const void *w_packed, const float *w_scale, const float *bias, void *y,
                       int64_t ldy, int32_t *acc_out, int64_t M, int64_t N, int64_t K, int bits,
-                      void *ws, size_t ws_bytes, hipStream_t stream, bool go = true) {
-  const fq::GemmPlan pl = fq::plan_gemm(M, N, K, bits, a_fmt == fq::kANibbleKM);
+                      void *ws, size_t ws_bytes, hipStream_t stream, const fq::GemmPlan &pl, bool go = true) {
   const size_t need = fq::gemm_plan_workspace(pl) + (a_fmt == fq::kANibble ? fq::gemm_plan_relayout_bytes(pl, M, K) : 0);
   if (need > 0 && (!ws || ws_bytes < need))
     return fail(FQ_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, ws ? ws_bytes : (size_t)0);
@@ -200,16 +199,16 @@ fq_status gemm_entry(int bits, const void *a_codes, const float *delta, const vo
                      span(bias, bias ? (size_t)N * 4 : 0)}))
     return fail(FQ_ERR_ALIAS, "y, acc_out and the workspace must not overlap each other or an input");
   return gemm_common(a_codes, a_fmt, lda, delta, w_packed, w_scale, bias, y, ldy, acc_out, M, N, K,
-                     bits, ws, ws_bytes, static_cast<hipStream_t>(stream));
+                     bits, ws, ws_bytes, static_cast<hipStream_t>(stream), fq::plan_gemm(M, N, K, bits));
 }
 
 // fq_linear workspace: none when one fused kernel runs the projection (few tokens, K up
-// to 4096); otherwise [codes (nibbles for W4A4, int8 for W8A8)][delta][split-K partials]
+// to 4096); otherwise [codes (4-bit for W4A4, int8 for W8A8)][delta][split-K partials]
 size_t linear_ws_bytes(int64_t M, int64_t N, int64_t K, int bits) {
   if (M <= 0 || N <= 0 || K < 128 || (bits != 4 && bits != 8)) return 0;
   if (fq::plan_small(M, N, K, bits).ok) return 0;
   return align256((size_t)M * (size_t)K * (size_t)bits / 8) + align256((size_t)M * 4) +
-         fq::gemm_plan_workspace(fq::plan_gemm(M, N, K, bits, bits == 4));
+         fq::gemm_plan_workspace(fq::plan_gemm(M, N, K, bits, true));
 }
 
 int log2_pow2(int b) {
@@ -270,22 +269,21 @@ fq_status linear_common(const void *x_bf16, int64_t ldx, const float *smooth_inv
   float *delta = reinterpret_cast<float *>(codes + codes_bytes);
   void *gws = codes + codes_bytes + delta_bytes;
   const size_t gws_bytes = ws_bytes - codes_bytes - delta_bytes;
-  // W4A4 codes between the two kernels are nibbles (half the bytes of int8, the same
-  // per-step cost in the GEMMs, which widen them in registers), canonical or, for the
-  // k-group GEMM, k-step major; W8A8 codes are int8.
-  const bool nibble = bits == 4;
-  const bool kmajor = nibble && fq::plan_gemm(M, N, K, bits, true).kind == 3;
-  const int fmt = nibble ? (kmajor ? fq::kOutNibbleKM : fq::kOutNibble) : fq::kOutInt8;
-  const int afmt = nibble ? (kmajor ? fq::kANibbleKM : fq::kANibble) : fq::kAInt8;
+  // W4A4 codes between the two kernels take 4 bits, W8A8 codes 8, canonical or, for the
+  // kernels that read them so, k major.
+  const fq::GemmPlan pl = fq::plan_gemm(M, N, K, bits, true);
+  const bool nibble = bits == 4, major = fq::plan_major_codes(pl, bits);
+  const int fmt = nibble ? (major ? fq::kOutF6Major : fq::kOutNibble) : fq::kOutInt8;
+  const int afmt = nibble ? (major ? fq::kAF6Major : fq::kANibble) : fq::kAInt8;
   const int64_t lda = nibble ? K / 2 : K;
   s = gemm_common(codes, afmt, lda, delta, w_packed, w_scale, bias, y_bf16, ldy, nullptr, M, N, K, bits, gws,
-                  gws_bytes, st, /*go=*/false);
+                  gws_bytes, st, pl, /*go=*/false);
   if (s != FQ_OK) return s;
   hipError_t e = fq::launch_fwht_quant(x_bf16, false, ldx, smooth_inv, post_inv, M, (int)K, b, bits,
                                        clip_ratio, inv_sqrt_pow2(b), codes, lda, delta, fmt, st);
   if (e != hipSuccess) return hip_fail(e, "fwht_quant launch");
   return gemm_common(codes, afmt, lda, delta, w_packed, w_scale, bias, y_bf16, ldy, nullptr, M, N, K, bits, gws,
-                     gws_bytes, st);
+                     gws_bytes, st, pl);
 }
 
 // Device address of `scratch` on the current device, looked up once per device with that

@@ -994,7 +994,7 @@ static constexpr size_t tile_lds_bytes() {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool kmajor_codes) {
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused) {
   GemmPlan pl{};
   const int ktot = (int)(K / kTileK);
   if (M <= 64) {
@@ -1063,29 +1063,49 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool kmajor_codes)
       }
     }
   } else {
-    // INT4 at long K where 128 x 128 tiles would not fill the chip without splitting K (a
-    // few hundred to ~1000 rows, N ~ 2048): 128 x 64 tiles with the K range split across
-    // the workgroup's four waves instead (gemm_kgroup_kernel, no partial buffer, no second
-    // kernel).  Measured at M = 816, K 16384 -> N 2048 against the split 128 x 128 plan:
-    // 31 against 43 us on one GPU (fed k-step-major codes).  Short K (fewer than 64 steps
-    // per tile) and grids of fewer than 160 tiles stay on the LDS-ring kernel below.
-    // With k-step-major codes for free (no conversion kernel), grids of up to 1023 such
-    // tiles at K >= 16384 take it too: K 16384 -> N 2048 at M = 1600 / 2048 / 3072 in
-    // 56.5 / 58.3 / 85.4 against 63.3 / 64.1 / 103.8 us on the LDS-ring kernel; at 1024
-    // tiles (M = 4096) the two measured the same and at K = 8192 the ring kernel led.
-    // Byte offsets into the codes and the weights are 32-bit in that kernel.
-    if (bits == 4 && ktot >= 64 && M * K / 2 < (int64_t(1) << 31) && N * K / 2 < (int64_t(1) << 31)) {
-      const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
-      const int64_t tkg = ((M + 127) / 128) * ((N + 63) / 64);
-      const bool wide = kmajor_codes && ktot >= 128 && tkg < 1024;
-      if ((t128 < 200 || wide) && tkg >= 160) {
-        pl.kind = 3;
-        pl.tiles = tkg;
-        pl.splits = 1;
-        pl.ksteps = ktot;
-        pl.partial_bytes = 0;
-        return pl;
-      }
+    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    const int64_t tkg = ((M + 127) / 128) * ((N + 63) / 64);
+    const int64_t t256 = ((M + 255) / 256) * ((N + 127) / 128);
+    // byte offsets into the codes and the weights are 32-bit in the kernels of kinds 3 and 4
+    const bool off32 = M * K * bits / 8 < (int64_t(1) << 31) && N * K * bits / 8 < (int64_t(1) << 31);
+    if (off32 && bits == 4 && fused && t128 > 256) {
+      // More than one 128 x 128 tile per compute unit: the wide-tile kernel (INT4 on the FP6
+      // matrix cores, from k-major codes), whose larger tiles move fewer operand bytes.  GEMM
+      // times against the LDS-ring kernel below, cold weights, one GPU: W4A4 K 16384 -> N 2048
+      // M = 4096 86 / 127 us, K 2048 -> N 8192 M = 640 16.4 / 21.2, -> N 16384 M = 333 17.4 / 21.5;
+      // W8A8 129 / 161, 21.6 / 25.4, K 2048 -> N 32768 M = 200 29 / 36.  (Split K for the
+      // W8A8 projection K 16384 -> N 2048 at M = 816, 256 workgroups: 42 + 6.7 us of epilogue
+      // against 40 + 5.2 on heavy-tailed tokens, not taken.)  With up to one tile per compute unit the LDS-ring kernel keeps more of the chip busy
+      // (W4A4 K 2048 -> N 8192 M = 512 15.3 / 15.1).
+      pl.kind = 4;
+      pl.tiles = t256;
+      pl.splits = 1;
+      pl.ksteps = ktot;
+      return pl;
+    }
+    if (off32 && bits == 4 && fused && ktot >= 32 && (tkg <= 256 || ktot >= 64) && (tkg >= 96 || ktot < 128)) {
+      // INT4, K >= 4096, at most one 128 x 64 tile per compute unit (two from K = 8192 on): the K
+      // range split across a workgroup's four waves (no partial buffer, no second kernel).
+      // Against the kernel below: K 4096 -> N 4096 M = 512 13.5 / 15.9 us, K 6144 -> N 1536
+      // M = 816 14.5 / 20.0, K 8192 -> N 2048 M = 333 16.4 / 19.7, K 16384 -> N 2048 M = 816
+      // 27.5 / 43, M = 1600 53 / 70; K 2048 -> N 2560 M = 512 10.0 / 9.8.  A grid of fewer than
+      // 96 tiles at K >= 16384 is faster with K split over workgroups (M = 200 25.2 / 19.8).
+      pl.kind = 3;
+      pl.tiles = tkg;
+      pl.splits = 1;
+      pl.ksteps = ktot;
+      return pl;
+    }
+    if (off32 && bits == 4 && !fused && ktot >= 64 && t128 < 200 && tkg >= 160) {
+      // Canonical codes: kind 3 still pays for their conversion (a kernel of its own) where
+      // 128 x 128 tiles would need a split K (K 16384 -> N 2048, M = 816: 35 us with the
+      // conversion against 43 us on one GPU).  Short K and grids of fewer than 160 tiles stay on
+      // the LDS-ring kernel below.
+      pl.kind = 3;
+      pl.tiles = tkg;
+      pl.splits = 1;
+      pl.ksteps = ktot;
+      return pl;
     }
     pl.kind = 1;
     // K slices: split a grid of fewer than 200 tiles while each slice keeps >= 32 steps
@@ -1100,10 +1120,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool kmajor_codes)
     // K 16384 -> N 2048 the split 128-row grid stays ahead, 39.7 against 43.1 us)
     pl.bm = 128;
     pl.bn = 128;
-    {
-      const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
-      if (t128 * slices(t128) <= 128) pl.bm = 64;
-    }
+    if (t128 * slices(t128) <= 128) pl.bm = 64;
     const int64_t tiles = ((M + pl.bm - 1) / pl.bm) * ((N + pl.bn - 1) / pl.bn);
     int64_t s = slices(tiles);
     pl.ksteps = (int)((ktot + s - 1) / s);
@@ -1252,7 +1269,7 @@ static hipError_t launch_gemm_t(const GemmParams &p, const GemmPlan &pl, hipStre
 hipError_t launch_gemm(const GemmArgs &g, const GemmPlan &pl, void *ws, hipStream_t s, bool go) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (pl.kind == 3) {
-    // k groups: k-step-major codes as given, or canonical ones converted into ws first
+    // k groups: k-major codes as given, or canonical ones converted into ws first
     if (g.bits != 4) return hipErrorInvalidValue;
     KgParams kp;
     kp.delta = g.delta;
@@ -1265,7 +1282,7 @@ hipError_t launch_gemm(const GemmArgs &g, const GemmPlan &pl, void *ws, hipStrea
     kp.M = (int)g.M;
     kp.N = (int)g.N;
     kp.K = (int)g.K;
-    if (g.a_fmt == kANibbleKM) {
+    if (g.a_fmt == kAF6Major) {
       kp.a = g.a;
       return launch_gemm_kgroup(kp, nullptr, nullptr, s, go);
     }
@@ -1289,9 +1306,14 @@ hipError_t launch_gemm(const GemmArgs &g, const GemmPlan &pl, void *ws, hipStrea
   p.ksteps = pl.ksteps;
   p.partial = pl.splits > 1 ? reinterpret_cast<int32_t *>(ws) : nullptr;
   p.order = pl.order;
+  if (pl.kind == 4) {
+    if (g.a_fmt != (g.bits == 4 ? kAF6Major : kAInt8) || g.lda != g.K * g.bits / 8) return hipErrorInvalidValue;
+    WideParams wp{g.a, g.delta, g.w, g.w_scale, g.bias, g.y, g.ldy, g.acc_out, p.M, p.N, p.K};
+    return launch_gemm_wide(wp, g.bits, s, go);
+  }
   if (g.bits == 4)
     return g.a_fmt == kANibble ? launch_gemm_t<4, kANibble>(p, pl, s, go) : hipErrorInvalidValue;
-  return launch_gemm_t<8, kAInt8>(p, pl, s, go);
+  return g.a_fmt == kAInt8 ? launch_gemm_t<8, kAInt8>(p, pl, s, go) : hipErrorInvalidValue;
 }
 
 // ----------------------------------------------------------------------------------------

@@ -1,99 +1,100 @@
 // Tiled INT4 GEMM for a few hundred to ~1000 tokens at long K (eq. (8) contraction and
-// rescale), where 128 x 128 output tiles would leave most compute units idle unless K is
+// rescale), where larger output tiles would leave most compute units idle unless K is
 // split across workgroups (and a second kernel adds the slices).
 //
-// Workgroup: 4 waves, one 128 x 64 output tile (8 x 4 tiles of 16 x 16); wave w owns the
+// Workgroup: 4 waves, one 128 x 64 output tile (4 x 2 tiles of 32 x 32); wave w owns the
 // k steps w, w + 4, w + 8, ... of the whole of K, so the tile needs no split of K across
 // workgroups and its four partial sums add up through LDS at the end (exact integers).
 // Every wave streams its own operands straight from L2 into registers, three register sets
-// deep (the loads of steps ks + 4 and ks + 8 are in flight while step ks is multiplied; two
-// sets measured the same to 6% slower at M = 816, K 16384 -> N 2048), with buffer
-// loads: one SGPR descriptor per operand, a fixed per-lane offset and a per-step scalar
-// offset, so the loop carries no address arithmetic.  No operand goes through LDS.
-//
-// Activation codes come k-step major: the 64 bytes (128 nibble codes) of row r for k step
-// ks sit at ks * 64 M + 64 r, so a row tile's operand of one step is 1 KB contiguous
-// (16 rows x 64 bytes), one coalesced load.  Read from the canonical row-major layout the
-// same operand is 16 half cache lines and the kernel measured 30% slower; the fused
-// projection's prologue writes this layout directly and the GEMM entry point converts
-// canonical codes first (codes_kmajor_kernel).
-//
-// MFMA and widening as in the other GEMM kernels: v_mfma_i32_16x16x64_i8 on nibbles widened
-// to int8 x 16 (channels interleaved 0 2 4 6 1 3 5 7 in both operands), INT32 accumulators
-// in AGPRs (this file is built without the VGPR accumulator form: 128 accumulators plus two
-// register sets of operands do not fit in 256 VGPRs), the factor 256 shifted out at the end.
+// deep, with buffer loads: one SGPR descriptor per operand, a fixed per-lane offset and a
+// per-step scalar offset, so the loop carries no address arithmetic.  No operand goes through LDS.
+// The products run on the FP6 matrix cores (fq_f6.hpp).  One wave per SIMD: the issue of the widening
+// (128 operations a step, 144 on INT8 operands) and of the multiplies (28 against 64 instructions)
+// bounds it.  M = 816, K 16384 -> N 2048: 28.5 us against 31.5 on INT8 operands.
 #include "fq_device.hpp"
+#include "fq_f6.hpp"
 #include "fq_launch.hpp"
 
 namespace fq {
 
 namespace {
 
-constexpr int kKgTI = 8;    // 16-row tiles per workgroup tile
-constexpr int kKgTJ = 4;    // 16-column tiles per workgroup tile
+constexpr int kKgTI = 4;    // 32-row tiles per workgroup tile
+constexpr int kKgTJ = 2;    // 32-column tiles per workgroup tile
 constexpr int kKgWaves = 4; // k groups
-constexpr int kKgShift = 8; // both operands widened x 16
 constexpr int kKgSets = 3;  // operand register sets: loads run two k steps ahead
-constexpr size_t kKgPartLds = (size_t)kKgWaves * kKgTI * kKgTJ * 1024;  // the k groups' sums
-constexpr int kKgOutStride = 16 * kKgTJ * 2 + 16;                        // bf16 staging row, padded
-constexpr size_t kKgLds = kKgPartLds + (size_t)16 * kKgTI * kKgOutStride;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, int64_t bytes) {
-  const int n = bytes < 0x7fffffff ? (int)bytes : 0x7fffffff;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, n, 0x00020000);
-}
+constexpr int kKgRows = 32 * kKgTI, kKgCols = 32 * kKgTJ;
+constexpr size_t kKgPartLds = (size_t)kKgWaves * kKgTI * kKgTJ * 4096;  // the k groups' sums
+constexpr int kKgOutStride = kKgCols * 2 + 16;                           // bf16 staging row, padded
+constexpr size_t kKgSumOff = kKgPartLds + (size_t)kKgRows * kKgOutStride;
+constexpr size_t kKgLds = kKgSumOff + (size_t)kKgWaves * (kKgRows + kKgCols) * 4;
 
 __global__ __launch_bounds__(64 * kKgWaves) void gemm_kgroup_kernel(KgParams p) {
   constexpr int TI = kKgTI, TJ = kKgTJ, KG = kKgWaves, NB = TI * TJ;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ntn = (p.N + 16 * TJ - 1) / (16 * TJ);
+  const int ntn = (p.N + kKgCols - 1) / kKgCols;
   const int tn = blockIdx.x % ntn, tm = blockIdx.x / ntn;
-  const int m0 = tm * 16 * TI, n0 = tn * 16 * TJ;
+  const int m0 = tm * kKgRows, n0 = tn * kKgCols;
   const int ktot = p.K / kTileK;
-  const int astep = p.M * 64;  // bytes of one k step of the k-major codes
+  const uint32_t astep = (uint32_t)p.M * 64u;  // bytes of one k step of the codes
+  const int u = lane >> 5, cl = lane & 31;
 
-  // per-lane operand offsets: row 16 i + l % 16 (rows past M repeat row M - 1, never
-  // stored), 16 bytes per lane group (channels 32 (l / 16) + [0, 32) of the step)
+  // rows: 32-row blocks of the k-major codes, half h of a step at + 32 h
   uint32_t aoff[TI];
 #pragma unroll
-  for (int i = 0; i < TI; ++i) aoff[i] = (uint32_t)min(m0 + 16 * i + (lane & 15), p.M - 1) * 64u + 16u * (lane >> 4);
-  // weight tile (nb, ks) at (nb K/128 + ks) KB, lane l's 16 bytes at 16 l (tiles past N
+  for (int i = 0; i < TI; ++i) aoff[i] = row_offset(m0 + 32 * i, p.M, lane);
+  // columns: lane l takes column l % 32 of a 32-column block and the k group 2 h + l / 32, 16
+  // bytes of weight tile (column / 16) at lane 16 (2 h + l / 32) + column % 16 (tiles past N
   // re-read the last one, never stored)
   uint32_t boff[TJ];
 #pragma unroll
-  for (int j = 0; j < TJ; ++j) boff[j] = (uint32_t)min(n0 / 16 + j, p.N / 16 - 1) * (uint32_t)ktot * 1024u + lane * 16;
+  for (int j = 0; j < TJ; ++j)
+    boff[j] = (uint32_t)min(n0 / 16 + 2 * j + (cl >> 4), p.N / 16 - 1) * (uint32_t)ktot * 1024u +
+              (uint32_t)(u * 16 + (cl & 15)) * 16u;
   const __amdgpu_buffer_rsrc_t arsrc = buffer_of(p.a, (int64_t)ktot * astep);
   const __amdgpu_buffer_rsrc_t brsrc = buffer_of(p.w, (int64_t)(p.N / 16) * ktot * 1024);
 
-  v4i acc[TI][TJ];
+  v16f acc[TI][TJ];
+  v4f rs[TI], cs[TJ];
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
+  for (int i = 0; i < TI; ++i) {
+    rs[i] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+  }
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) cs[j] = v4f{0.f, 0.f, 0.f, 0.f};
+  const v8i pat = f6_row_pattern(lane);
   constexpr int NSET = kKgSets;
-  v4i ra[NSET][TI], rb[NSET][TJ];
-  auto load = [&](v4i (&ra_)[TI], v4i (&rb_)[TJ], int ks) {
+  v4i ra[NSET][2][TI], rb[NSET][2][TJ];
+  auto load = [&](v4i (&ra_)[2][TI], v4i (&rb_)[2][TJ], int ks) {
 #pragma unroll
-    for (int i = 0; i < TI; ++i) ra_[i] = __builtin_amdgcn_raw_buffer_load_b128(arsrc, aoff[i], ks * astep, 0);
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) rb_[j] = __builtin_amdgcn_raw_buffer_load_b128(brsrc, boff[j], ks * 1024, 0);
+      for (int j = 0; j < TJ; ++j) rb_[h][j] = __builtin_amdgcn_raw_buffer_load_b128(brsrc, boff[j] + h * 512u, ks * 1024u, 0);
+#pragma unroll
+      for (int i = 0; i < TI; ++i) ra_[h][i] = __builtin_amdgcn_raw_buffer_load_b128(arsrc, aoff[i] + h * 32u, ks * astep, 0);
+    }
   };
-  // both 64-channel chunks of a step: the widened weight operands of the chunk, then each
-  // row tile's widened activation operand against the four of them
-  auto compute = [&](const v4i (&ra_)[TI], const v4i (&rb_)[TJ]) {
+  auto compute = [&](const v4i (&ra_)[2][TI], const v4i (&rb_)[2][TJ]) {
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      v4i wb[TJ];
+    for (int h = 0; h < 2; ++h) {
+      v8i fb[TJ];
 #pragma unroll
-      for (int j = 0; j < TJ; ++j) wb[j] = widen8(c == 0 ? v2i{rb_[j].x, rb_[j].y} : v2i{rb_[j].z, rb_[j].w});
+      for (int j = 0; j < TJ; ++j) fb[j] = spread32(rb_[h][j]);
 #pragma unroll
       for (int i = 0; i < TI; ++i) {
-        const v4i wa = widen8(c == 0 ? v2i{ra_[i].x, ra_[i].y} : v2i{ra_[i].z, ra_[i].w});
+        const v8i fa = expand32(ra_[h][i]);
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = mfma16x16x64(wa, wb[j], acc[i][j]);
+        for (int j = 0; j < TJ; ++j) acc[i][j] = mfma_f6_32(fa, fb[j], acc[i][j]);
+        rs[i] = mfma_f6_16(fa, pat, rs[i]);
       }
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) cs[j] = mfma_f6_16(pat, fb[j], cs[j]);
     }
   };
   // NSET steps per loop trip, one per register set, each set's loads issued NSET - 1 steps
@@ -121,65 +122,64 @@ __global__ __launch_bounds__(64 * kKgWaves) void gemm_kgroup_kernel(KgParams p) 
   for (int q = 0; q < NSET - 1; ++q)
     if (t + q < nk) compute(ra[q], rb[q]);
 
-  // ---- the k groups' sums: every wave leaves its 32 tiles in LDS (lane-major, 1 KB per
-  // tile), then wave w adds up column tile w of all four and rescales it ----
-  v4i *part = reinterpret_cast<v4i *>(lds);
+  // ---- the k groups' sums: every wave leaves its 8 tiles (lane-major) and its sums of codes in
+  // LDS, then wave w adds up and rescales row block w of all four ----
+  v4f *part = reinterpret_cast<v4f *>(lds);
+  int *rsum = reinterpret_cast<int *>(lds + kKgSumOff), *csum = rsum + KG * kKgRows;
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) part[(wave * NB + i * TJ + j) * 64 + lane] = acc[i][j];
-  __syncthreads();
-  static_assert(TJ == KG, "one column tile per wave in the final sum");
-  const int j = wave;
-  const int g = lane >> 4, cl = lane & 15;
-  v4i fin[TI];
+    for (int j = 0; j < TJ; ++j)
 #pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    v4i s = part[(i * TJ + j) * 64 + lane];
-#pragma unroll
-    for (int q = 1; q < KG; ++q) {
-      const v4i u = part[(q * NB + i * TJ + j) * 64 + lane];
-      s.x += u.x;
-      s.y += u.y;
-      s.z += u.z;
-      s.w += u.w;
-    }
-    fin[i] = s;
-  }
-  // rescale factors: the rows' delta_t (rows past M read row M - 1, never stored) and the
-  // column's s_j and b_j
-  float dt[TI][4];
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) dt[i][r] = p.delta[min(m0 + 16 * i + 4 * g + r, p.M - 1)];
-  const int n = n0 + 16 * j + cl;
-  const int nc = min(n, p.N - 1);
-  const float sw = p.w_scale[nc];
-  const float bj = p.bias ? p.bias[nc] : 0.0f;
-  if (p.acc_out) {
+      for (int e4 = 0; e4 < 4; ++e4)
+        part[((wave * NB + i * TJ + j) * 4 + e4) * 64 + lane] =
+            v4f{acc[i][j][4 * e4], acc[i][j][4 * e4 + 1], acc[i][j][4 * e4 + 2], acc[i][j][4 * e4 + 3]};
+  if ((lane & 15) < 2)
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + 16 * i + 4 * g + r;
-        if (m < p.M && n < p.N) p.acc_out[(int64_t)m * p.N + n] = fin[i][r] >> kKgShift;
-      }
-  }
-  // bf16 y = fp32(acc) (s_j delta_t) + b_j, staged in LDS (after the partial sums) so that
-  // the tile leaves in 16-byte row chunks
-  uint8_t *out = lds + kKgPartLds;
+      for (int r = 0; r < 4; ++r)
+        rsum[wave * kKgRows + 32 * i + (lane & 1) * 16 + 4 * (lane >> 4) + r] = (int)(rs[i][r] * 8.0f);
+  if (lane < 16)
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = 16 * i + 4 * g + r;
-      const float v = (float)(fin[i][r] >> kKgShift) * (sw * dt[i][r]) + bj;
-      *reinterpret_cast<uint16_t *>(out + row * kKgOutStride + (16 * j + cl) * 2) = (uint16_t)f32_to_bf16(v);
+    for (int j = 0; j < TJ; ++j) {
+      csum[wave * kKgCols + 32 * j + lane] = (int)(cs[j][0] * 8.0f);
+      csum[wave * kKgCols + 32 * j + 16 + lane] = (int)(cs[j][1] * 8.0f);
     }
   __syncthreads();
-  constexpr int CPR = 16 * TJ / 8;  // 16-byte chunks per staged row
-  for (int q = threadIdx.x; q < 16 * TI * CPR; q += 64 * KG) {
+  static_assert(TI == KG, "one row block per wave in the final sum");
+  uint8_t *out = lds + kKgPartLds;
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) {
+    const int col = 32 * j + cl, n = n0 + col, nc = min(n, p.N - 1);
+    const float sw = p.w_scale[nc];
+    const float bj = p.bias ? p.bias[nc] : 0.0f;
+    int cc = 64 * p.K;
+#pragma unroll
+    for (int q = 0; q < KG; ++q) cc -= 8 * csum[q * kKgCols + col];
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) {
+      v4f s = part[((wave * TJ + j) * 4 + e4) * 64 + lane];
+#pragma unroll
+      for (int q = 1; q < KG; ++q) s += part[((q * NB + wave * TJ + j) * 4 + e4) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = 32 * wave + 8 * e4 + 4 * u + e, m = m0 + row;
+        int r = 0;
+#pragma unroll
+        for (int q = 0; q < KG; ++q) r += rsum[q * kKgRows + row];
+        const int sum = (int)(s[e] * 64.0f) + cc - 8 * r;
+        if (p.acc_out && m < p.M && n < p.N) p.acc_out[(int64_t)m * p.N + n] = sum;
+        // rows past M read row M - 1's delta, never stored
+        const float v = (float)sum * (sw * p.delta[min(m, p.M - 1)]) + bj;
+        *reinterpret_cast<uint16_t *>(out + row * kKgOutStride + col * 2) = (uint16_t)f32_to_bf16(v);
+      }
+    }
+  }
+  // bf16 rows staged in LDS (after the partial sums) so that the tile leaves in 16-byte row chunks
+  __syncthreads();
+  constexpr int CPR = kKgCols / 8;  // 16-byte chunks per staged row
+  for (int q = threadIdx.x; q < kKgRows * CPR; q += 64 * KG) {
     const int row = q / CPR, ch = q % CPR;
     const int m = m0 + row, nn = n0 + ch * 8;
     if (m < p.M && nn < p.N)
@@ -187,13 +187,12 @@ __global__ __launch_bounds__(64 * kKgWaves) void gemm_kgroup_kernel(KgParams p) 
   }
 }
 
-// Canonical nibble codes [M][K/2] -> k-step major [K/128][M][64 B], 16 bytes per thread.
+// Canonical nibble codes [M][K/2] -> the prologue's arrangement, k major, 16 bytes per thread.
 // Thread u takes 16-byte chunk c = 16 kq + u % 16 of row r = (u / 16) % M, kq = u / (16 M):
 // a wave reads 4 rows x 256 contiguous bytes (whole cache lines) and writes, for each of
 // the 4 k steps those bytes hold, 4 consecutive rows x 64 bytes (256 contiguous bytes).
-// (Read as a quarter step per thread, the rows' cache lines were fetched twice.)
-__global__ __launch_bounds__(256) void codes_kmajor_kernel(const uint8_t *__restrict__ src, uint8_t *__restrict__ dst,
-                                                            int M, int K) {
+__global__ __launch_bounds__(256) void codes_major_kernel(const uint8_t *__restrict__ src, uint8_t *__restrict__ dst,
+                                                          int M, int K) {
   const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int cpr = K / 32;  // 16-byte chunks per row (4 per k step)
   const int64_t rowunits = (int64_t)M * 16;
@@ -202,28 +201,26 @@ __global__ __launch_bounds__(256) void codes_kmajor_kernel(const uint8_t *__rest
   const int r = rem >> 4;
   const int c = 16 * kq + (rem & 15);
   if (c >= cpr) return;
-  const int ks = c >> 2;
-  *reinterpret_cast<uint4 *>(dst + (int64_t)ks * 64 * M + (int64_t)r * 64 + (c & 3) * 16) =
-      *reinterpret_cast<const uint4 *>(src + (int64_t)r * (K / 2) + (int64_t)c * 16);
+  const uint4 x = *reinterpret_cast<const uint4 *>(src + (int64_t)r * (K / 2) + (int64_t)c * 16);
+  const uint2 lo = rearrange16(x.x, x.y), hi = rearrange16(x.z, x.w);
+  *reinterpret_cast<uint4 *>(dst + major_chunk(r, M, c)) = make_uint4(lo.x, lo.y, hi.x, hi.y);
 }
 
 }  // namespace
 
-size_t kgroup_lds_bytes() { return kKgLds; }
-
-hipError_t launch_gemm_kgroup(const KgParams &p, const uint8_t *a_canonical, uint8_t *a_kmajor, hipStream_t s,
+hipError_t launch_gemm_kgroup(const KgParams &p, const uint8_t *a_canonical, uint8_t *a_major, hipStream_t s,
                               bool go) {
   static std::atomic<uint64_t> attr{0};
   hipError_t e = allow_dynamic_lds(&gemm_kgroup_kernel, kKgLds, attr);
   if (e != hipSuccess || !go) return e;
   if (a_canonical) {
     const int64_t units = (int64_t)((p.K / 32 + 15) / 16) * p.M * 16;  // 16-chunk row groups, rounded up
-    hipLaunchKernelGGL(codes_kmajor_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s, a_canonical,
-                       a_kmajor, p.M, p.K);
+    hipLaunchKernelGGL(codes_major_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s, a_canonical,
+                       a_major, p.M, p.K);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const int64_t tiles = ((int64_t)(p.M + 16 * kKgTI - 1) / (16 * kKgTI)) * ((p.N + 16 * kKgTJ - 1) / (16 * kKgTJ));
+  const int64_t tiles = ((int64_t)(p.M + kKgRows - 1) / kKgRows) * ((p.N + kKgCols - 1) / kKgCols);
   hipLaunchKernelGGL(gemm_kgroup_kernel, dim3((unsigned)tiles), dim3(64 * kKgWaves), kKgLds, s, p);
   return hipGetLastError();
 }

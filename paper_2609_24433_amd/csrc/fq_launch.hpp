@@ -31,12 +31,18 @@ inline hipError_t allow_dynamic_lds(Kern kern, size_t lds, std::atomic<uint64_t>
 // Output layouts of the prologue.
 constexpr int kOutNibble = 0;    // canonical signed-INT4: channel 2i low nibble of byte i
 constexpr int kOutInt8 = 1;      // canonical int8, one byte per channel
-constexpr int kOutNibbleKM = 2;  // the same nibbles k-step major: [K/128][M][64 B]
+constexpr int kOutF6Major = 2;  // 4-bit codes k major, arranged for six-bit fields (pack_chunk_f6)
+
+// K major: a row's 4-bit codes go in pieces of 64 bytes (one k step), piece by piece for all rows,
+// [K/128][M][64 B].  Byte offset of 16-byte chunk c of a row.
+__host__ __device__ inline int64_t major_chunk(int64_t row, int64_t M, int c) {
+  return (((int64_t)(c >> 2) * M + row) * 4 + (c & 3)) * 16;
+}
 
 // Activation operand formats of the GEMM.
 constexpr int kANibble = 0;    // canonical nibbles (widened in the kernel)
 constexpr int kAInt8 = 1;      // canonical int8 (W8A8)
-constexpr int kANibbleKM = 2;  // nibbles k-step major: [K/128][M][64 B] (plan kind 3)
+constexpr int kAF6Major = 2;   // kOutF6Major (INT4, plan kinds 3 and 4)
 
 hipError_t launch_fwht_quant(const void *x, bool x_is_f32, int64_t ldx, const float *chan_mult,
                              const float *post_mult, int64_t M, int K, int b, int bits, float clip_ratio, float cb,
@@ -58,7 +64,8 @@ hipError_t launch_unpack_weights(const uint8_t *packed, int64_t N, int K, int bi
 // GEMM plan: which kernel, its tiling and its split of K.
 struct GemmPlan {
   int kind;     // 0 = streaming (M <= 64), 1 = tiled, 2 = streaming with one K range per wave (long K),
-                // 3 = k groups (INT4, a few hundred rows, long K; k-step-major codes)
+                // 3 = k groups (INT4, a few hundred rows, long K), 4 = wide tiles; both read INT4
+                // codes k major
   int mt;       // streaming: 16-row tiles covering M
   int kt, wk;   // streaming: k steps per wave, wave groups along K per workgroup
   int wc;       // streaming: 16-channel wave columns per workgroup
@@ -73,17 +80,19 @@ struct GemmPlan {
   size_t partial_bytes; // split-K INT32 partials [splits][M][N]
 };
 
-// kmajor_codes: the caller writes the activation codes k-step major at no extra cost (the
-// fused projection's prologue), which widens the k-group plan's range
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool kmajor_codes = false);
+// fused: the fused projection, whose prologue writes the codes k major at no extra cost where
+// the plan wants them so (plan_major_codes), which opens plan kind 4 to INT4 and widens kind 3's
+// range.
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused = false);
+inline bool plan_major_codes(const GemmPlan &pl, int bits) { return bits == 4 && (pl.kind == 3 || pl.kind == 4); }
 // scratch of the GEMM itself (split-K partials); a kind-3 plan fed canonical codes also
-// needs gemm_plan_relayout_bytes for their k-step-major copy
+// needs gemm_plan_relayout_bytes for their k-major copy
 size_t gemm_plan_workspace(const GemmPlan &pl);
 size_t gemm_plan_relayout_bytes(const GemmPlan &pl, int64_t M, int64_t K);
 
-// k-group GEMM (fq_gemm_kg.hip), plan kind 3: INT4 codes k-step major (a_fmt kANibbleKM).
+// k-group GEMM (fq_gemm_kg.hip), plan kind 3: INT4 k-major codes (a_fmt kAF6Major).
 struct KgParams {
-  const uint8_t *a;  // [K/128][M][64 B]
+  const uint8_t *a;
   const float *delta;
   const uint8_t *w;
   const float *w_scale;
@@ -93,11 +102,24 @@ struct KgParams {
   int32_t *acc_out;
   int M, N, K;
 };
-size_t kgroup_lds_bytes();
-// a_canonical != NULL: first convert those canonical codes into a_kmajor (M K/2 bytes),
+// a_canonical != NULL: first convert those canonical codes into a_major (M K/2 bytes),
 // which p.a must point to.  go = false only resolves the kernel and raises its LDS limit.
-hipError_t launch_gemm_kgroup(const KgParams &p, const uint8_t *a_canonical, uint8_t *a_kmajor, hipStream_t s,
+hipError_t launch_gemm_kgroup(const KgParams &p, const uint8_t *a_canonical, uint8_t *a_major, hipStream_t s,
                               bool go);
+
+// Wide-tile GEMM (fq_gemm_wide.hip), plan kind 4: k-major codes, 256 x 128 output tiles.
+struct WideParams {
+  const uint8_t *a;
+  const float *delta;
+  const uint8_t *w;
+  const float *w_scale;
+  const float *bias;
+  uint16_t *y;
+  int64_t ldy;
+  int32_t *acc_out;
+  int M, N, K;
+};
+hipError_t launch_gemm_wide(const WideParams &p, int bits, hipStream_t s, bool go);
 
 struct GemmArgs {
   const uint8_t *a;

@@ -34,8 +34,7 @@ struct QuantParams {
   float clip_ratio;
   float cb;  // float nearest 1/sqrt(b)
   uint8_t *codes;
-  int64_t ld_codes;  // bytes per output row (64 for k-step-major nibbles)
-  int64_t kstride;   // nibbles: bytes between the 128-channel k steps of a row (64 canonical)
+  int64_t ld_codes;  // bytes per output row (canonical layouts)
   float *delta;
   int out_fmt;
   int tpr_log2;
@@ -189,7 +188,7 @@ __global__ __launch_bounds__(NT) void fwht_quant_kernel(QuantParams p) {
     for (int c = 0; c < CPT; ++c) {
       const int j = c * TPR + lam;
       if (j < nchunks) {
-        if constexpr (OUT == kOutNibble) {
+        if constexpr (OUT == kOutNibble || OUT == kOutF6Major) {
           uint32_t cc[16];
           if (clamp) {
 #pragma unroll
@@ -198,8 +197,11 @@ __global__ __launch_bounds__(NT) void fwht_quant_kernel(QuantParams p) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) cc[i] = quantize_bits_biased<false>(v1[c][i], inv_l, lim);
           }
-          *reinterpret_cast<uint2 *>(row_out + (int64_t)(j >> 3) * p.kstride + (j & 7) * 8) =
-              pack_chunk_nibbles_biased(cc);
+          if constexpr (OUT == kOutNibble)
+            *reinterpret_cast<uint2 *>(row_out + (int64_t)j * 8) = pack_chunk_nibbles_biased(cc);
+          else
+            *reinterpret_cast<uint2 *>(p.codes + major_chunk(row, p.M, j >> 1) + (j & 1) * 8) =
+                pack_chunk_f6(cc);
         } else {
           int cc[16];
           if (clamp) {
@@ -274,6 +276,9 @@ static hipError_t launch_b(const QuantParams &p, const QuantShape &q, int grid, 
     if (clamp || p.out_fmt != kOutInt8) return hipErrorInvalidValue;
     return launch_m<Tin, LOG2B, false, kOutInt8>(p, q, grid, s);
   } else {
+    if (p.out_fmt == kOutF6Major)
+      return clamp ? launch_m<Tin, LOG2B, true, kOutF6Major>(p, q, grid, s)
+                   : launch_m<Tin, LOG2B, false, kOutF6Major>(p, q, grid, s);
     if (p.out_fmt == kOutNibble)
       return clamp ? launch_m<Tin, LOG2B, true, kOutNibble>(p, q, grid, s)
                    : launch_m<Tin, LOG2B, false, kOutNibble>(p, q, grid, s);
@@ -322,14 +327,8 @@ hipError_t launch_fwht_quant(const void *x, bool x_is_f32, int64_t ldx, const fl
   p.cb = cb;
   p.codes = codes;
   p.ld_codes = ld_codes;
-  p.kstride = 64;
   p.delta = delta;
   p.out_fmt = out_fmt;
-  if (out_fmt == kOutNibbleKM) {  // row r, k step ks at ks * 64 M + 64 r
-    p.out_fmt = kOutNibble;
-    p.ld_codes = 64;
-    p.kstride = 64 * M;
-  }
   p.tpr_log2 = q.tpr_log2;
   return x_is_f32 ? launch_t<float>(p, log2b, q, (int)grid64, s)
                   : launch_t<uint16_t>(p, log2b, q, (int)grid64, s);
