@@ -1068,7 +1068,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused) {
     const int64_t t256 = ((M + 255) / 256) * ((N + 127) / 128);
     // byte offsets into the codes and the weights are 32-bit in the kernels of kinds 3 and 4
     const bool off32 = M * K * bits / 8 < (int64_t(1) << 31) && N * K * bits / 8 < (int64_t(1) << 31);
-    if (off32 && bits == 4 && fused && t128 > 256) {
+    if (off32 && (bits == 8 || fused) && t128 > 256) {
       // More than one 128 x 128 tile per compute unit: the wide-tile kernel (INT4 on the FP6
       // matrix cores, from k-major codes), whose larger tiles move fewer operand bytes.  GEMM
       // times against the LDS-ring kernel below, cold weights, one GPU: W4A4 K 16384 -> N 2048

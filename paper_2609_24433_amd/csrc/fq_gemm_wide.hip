@@ -15,7 +15,18 @@ namespace fq {
 
 namespace {
 
+typedef int v16i __attribute__((ext_vector_type(16)));
+
 constexpr int kBN = 128;  // columns of an output tile (256 rows)
+
+// 16 bytes per lane from a buffer straight into LDS (lane l -> dst + 16 l).
+__device__ __forceinline__ void buffer_to_lds16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, void *dst) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, voff, soff, 0, 0);
+#else
+  (void)r; (void)voff; (void)soff; (void)dst;
+#endif
+}
 
 // Tile (tm, tn) of a workgroup.  The hardware hands workgroup p to XCD p % 8;
 // consecutive logical ids go to one XCD, and ids run down kGroup row tiles before the next
@@ -85,6 +96,136 @@ __device__ __forceinline__ void write_out(const WideParams &p, F sums, uint8_t *
   }
 }
 
+
+// ---------------- INT8 ----------------
+// 4 x 1 waves of 64 x 128 (one per SIMD, 128 accumulators each), canonical codes.  Both operands go
+// through a ring of k steps in LDS.  M = 4096, K 16384 -> N 2048: 123 us against 155 on the
+// 128 x 128 tiles (2.2 against 1.8 POPS).  Measured and not kept: 8 waves of 64 x 64 (128-135 us,
+// twice the LDS reads), rows straight into registers from a k-major copy written by the prologue
+// (113 us, but the scattered 16-byte stores cost the prologue 14 us).
+constexpr int k8Waves = 4, k8BM = 256, k8Stages = 3;
+constexpr int k8A = k8BM * 128, k8W = kBN / 16 * 2048, k8Stage = k8A + k8W;  // bytes per k step
+constexpr size_t k8Lds = (size_t)k8Stages * k8Stage + k8BM * 4;
+
+__global__ __launch_bounds__(64 * k8Waves) void gemm_wide8_kernel(WideParams p) {
+  constexpr int TI = 2, TJ = 4;
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  float *sdelta = reinterpret_cast<float *>(lds + (size_t)k8Stages * k8Stage);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ntm = (p.M + k8BM - 1) / k8BM, ntn = (p.N + kBN - 1) / kBN;
+  int tm, tn;
+  tile_of(blockIdx.x, gridDim.x, ntm, ntn, tm, tn);
+  const int m0 = tm * k8BM, n0 = tn * kBN;
+  const int ktot = p.K / kTileK;
+  sdelta[tid] = p.delta[min(m0 + tid, p.M - 1)];
+
+  // ring loads of one k step: wave w fills KBs [8 w, 8 w + 8) of the rows (8 rows x 128 bytes
+  // each, 16-byte chunks XOR-swizzled by (row >> 1) & 7) and [4 w, 4 w + 4) of the weights (a
+  // tile's chunk c at c ^ ((c >> 4) & 1): a wave reads every second chunk)
+  constexpr int IA = k8A / 1024 / k8Waves, IB = k8W / 1024 / k8Waves, LPS = IA + IB;
+  uint32_t avoff[IA], bvoff[IB];
+#pragma unroll
+  for (int i = 0; i < IA; ++i) {
+    const int row = (wave * IA + i) * 8 + (lane >> 3);
+    avoff[i] = (uint32_t)min(m0 + row, p.M - 1) * (uint32_t)p.K + ((lane & 7) ^ ((row >> 1) & 7)) * 16u;
+  }
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    const int kb = wave * IB + i;
+    bvoff[i] = (uint32_t)min(n0 / 16 + kb / 2, p.N / 16 - 1) * (uint32_t)ktot * 2048u + (kb & 1) * 1024u +
+               (lane ^ ((lane >> 4) & 1)) * 16u;
+  }
+  const __amdgpu_buffer_rsrc_t ar = buffer_of(p.a, (int64_t)p.M * p.K);
+  const __amdgpu_buffer_rsrc_t br = buffer_of(p.w, (int64_t)p.N * p.K);
+  // load q of step ks (clamped to the last step: past it only slots that are never read fill)
+  auto issue = [&](int ks, int slot, int q) {
+    const uint32_t kc = (uint32_t)min(ks, ktot - 1);
+    uint8_t *st = lds + slot * k8Stage;
+    if (q < IA) buffer_to_lds16(ar, avoff[q], kc * 128u, st + (wave * IA + q) * 1024);
+    else buffer_to_lds16(br, bvoff[q - IA], kc * 2048u, st + k8A + (wave * IB + q - IA) * 1024);
+  };
+
+  // operands of chunk q (32 channels): lane l takes row (or column) l % 32 and the 16 channels
+  // 32 q + 16 (l / 32) + [0, 16)
+  const int u = lane >> 5, r32 = lane & 31;
+  const int abase = (wave * 64 + r32) * 128 + ((u ^ ((r32 >> 1) & 7)) * 16);
+  const int bbase = k8A + (r32 >> 4) * 2048 + (((r32 & 15) * 2 + u) ^ ((r32 >> 3) & 1)) * 16;
+  v4i ra[2][TI], rb[2][TJ];
+  constexpr int NRD = TI + TJ;
+  auto read = [&](int set, int slot, int q, int r) {  // in the order the multiplies want them
+    const uint8_t *st = lds + slot * k8Stage;
+    if (r == 0) rb[set][0] = *reinterpret_cast<const v4i *>(st + bbase + q * 512);
+    else if (r <= TI) ra[set][r - 1] = *reinterpret_cast<const v4i *>(st + (abase ^ (q * 32)) + (r - 1) * 4096);
+    else rb[set][r - TI] = *reinterpret_cast<const v4i *>(st + bbase + q * 512 + (r - TI) * 4096);
+  };
+
+  v16i acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
+
+#pragma unroll
+  for (int q = 0; q < LPS; ++q) issue(0, 0, q);
+#pragma unroll
+  for (int q = 0; q < LPS; ++q) issue(1, 1, q);
+  wait_vmcnt<LPS>();
+  lds_barrier();
+#pragma unroll
+  for (int r = 0; r < NRD; ++r) read(0, 0, 0, r);
+#pragma unroll
+  for (int q = 0; q < LPS / 2; ++q) issue(2, 2, q);
+
+  int slot = 0;
+  for (int ks = 0; ks < ktot; ++ks) {
+    const int next = slot == k8Stages - 1 ? 0 : slot + 1;
+    const int prev = slot == 0 ? k8Stages - 1 : slot - 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int cur = q & 1;
+      int r = 0, g = 0;
+#pragma unroll
+      for (int t = 0; t < TI * TJ; ++t) {
+        const int i = t % TI, j = t / TI;
+        __builtin_amdgcn_sched_barrier(0);
+        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ra[cur][i], rb[cur][j], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (q == 3 && t == 1) {
+          // every read of this step's slot is done; the next step's loads have landed (step
+          // ks + 2's are the LPS later ones)
+          wait_vmcnt<LPS>();
+          lds_barrier();
+        }
+        if (q < 3 || t >= 1) {
+          // the next chunk's operands, two reads per multiply
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            if (r < NRD) {
+              read(cur ^ 1, q == 3 ? next : slot, (q + 1) & 3, r);
+              ++r;
+            }
+        }
+        // step ks + 2's second half in chunk 0, step ks + 3's first half after the barrier
+        if (q == 0 && g < LPS / 2) {
+          issue(ks + 2, prev, LPS / 2 + g);
+          ++g;
+        }
+        if (q == 3 && t >= 1 && g < LPS / 2) {
+          issue(ks + 3, slot, g);
+          ++g;
+        }
+      }
+    }
+    slot = next;
+  }
+  wait_vmcnt<0>();
+  __syncthreads();  // the ring's trailing loads and reads are over: LDS is reused
+  auto sums = [&](int i, int j, int e) -> int { return acc[i][j][e]; };
+  write_out<TI, TJ>(p, sums, lds, sdelta, wave, wave * 64, 0, m0, n0);
+}
 
 // ---------------- INT4 on the FP6 matrix cores ----------------
 // 8 x 1 waves (two per SIMD) of 32 x 128, k-major codes (kAF6Major).  A wave's 32 rows go straight
@@ -256,12 +397,18 @@ __global__ __launch_bounds__(64 * k4Waves) void gemm_wide4_kernel(WideParams p) 
 }  // namespace
 
 hipError_t launch_gemm_wide(const WideParams &p, int bits, hipStream_t s, bool go) {
-  static std::atomic<uint64_t> attr4{0};
-  if (bits != 4) return hipErrorInvalidValue;
+  static std::atomic<uint64_t> attr4{0}, attr8{0};
   const int64_t tiles = ((int64_t)(p.M + 255) / 256) * ((p.N + kBN - 1) / kBN);
-  hipError_t e = allow_dynamic_lds(&gemm_wide4_kernel, k4Lds, attr4);
-  if (e != hipSuccess || !go) return e;
-  hipLaunchKernelGGL(gemm_wide4_kernel, dim3((unsigned)tiles), dim3(64 * k4Waves), k4Lds, s, p);
+  hipError_t e;
+  if (bits == 4) {
+    e = allow_dynamic_lds(&gemm_wide4_kernel, k4Lds, attr4);
+    if (e != hipSuccess || !go) return e;
+    hipLaunchKernelGGL(gemm_wide4_kernel, dim3((unsigned)tiles), dim3(64 * k4Waves), k4Lds, s, p);
+  } else {
+    e = allow_dynamic_lds(&gemm_wide8_kernel, k8Lds, attr8);
+    if (e != hipSuccess || !go) return e;
+    hipLaunchKernelGGL(gemm_wide8_kernel, dim3((unsigned)tiles), dim3(64 * k8Waves), k8Lds, s, p);
+  }
   return hipGetLastError();
 }
 
