@@ -5,18 +5,23 @@
 //   transform: the prologue's transform alone (fold-before multiplier, unnormalized
 //     blockwise butterfly in the prologue's stage order, fold-after multiplier), fp32
 //     rows out; it gives the calibration tokens Z and the folded weight rows;
-//   second moment: G = sum_t z_t z_t^T in fp64 (a register-tiled fp64 product);
+//   second moment: G = sum_t z_t z_t^T in fp64 on the matrix cores, operands from registers;
 //   factor: U upper triangular with (G + lambda I)^-1 = U^T U.  With the index reversal
 //     P, the lower Cholesky factor L of A = P H P gives H = V V^T for the upper triangular
-//     V = P L P, so U = V^-1 = P L^-1 P: a blocked Cholesky (64-wide diagonal blocks in
-//     one wave's registers, row-parallel triangular solves, fp64 product updates of the
-//     trailing matrix) and a triangular inverse that merges neighbouring diagonal blocks
-//     level by level, so its large products run with many tiles;
+//     V = P L P, so U = V^-1 = P L^-1 P: a blocked Cholesky of one launch per 64 columns (panel,
+//     trailing update and the next diagonal block's factor and inverse together) and a
+//     triangular inverse that merges neighbouring diagonal blocks level by level, two launches
+//     a level;
 //   sweep: the lazy-batch column sweep in fp64, 128 columns per block: inside a block the
-//     columns are rounded one at a time for 4 rows per workgroup with the rows' block in
-//     LDS; after the block one fp64 product pushes the block's errors onto the later
+//     columns are rounded one at a time by a wave that holds its rows in registers; after the
+//     block one fp64 product pushes the block's errors onto the later
 //     columns.  Every operation and its order follow the fp64 contract of the sweep, so the
 //     codes are reproducible bit for bit.
+// The fp64 matrix instruction (42 TFLOP/s measured with four chains per wave) adds its four
+// products one after the other with one rounding each, so a chain of instructions is the
+// chain of fused multiply-adds that the contract asks for.  K = 1024, N = 1536, T = 2048: second
+// moment 92 us (502 before), factor 0.52 ms (2.7: one wave per diagonal block, row-parallel solves
+// with divisions, one launch per product), sweep 0.27 ms (1.2: barriers and a division per column).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -78,12 +83,11 @@ hipError_t launch_transform(const void *x, bool x_is_f32, int64_t ldx, const flo
 
 // ---------------------------------------------------------------------------------------
 // fp64 product update: C (op)= sum_k A[i][k] B[k][j], every element's sum an fma chain in
-// ascending k from +0, then C = C - sum, C = C + sum, C = -sum or C = sum.  64 x 64 tiles,
-// 4 x 4 per thread, k in chunks of 16 through LDS.  A and B are addressed through element
-// strides, so transposed operands need no copy.  `lower` computes only tiles on or below
-// the diagonal and writes elements with i >= j; `mirror` also writes C[j][i].
+// ascending k from +0, then C = C - sum, C = -sum or C = sum, on the fp64 matrix
+// instruction.  A and B are addressed through element strides, so transposed operands need no
+// copy.
 
-enum : int { kSub = 0, kAdd = 1, kSetNeg = 2, kSet = 3 };
+enum : int { kSub = 0, kSetNeg = 1, kSet = 2 };
 
 struct DProd {
   const void *a;
@@ -94,75 +98,86 @@ struct DProd {
   int64_t ldc;
   int64_t m, n, kd;
   int mode;
-  int lower, mirror;
   int kskip;  // B is lower triangular: tile column j0 sums k >= j0 only (the rest are zeros)
-  int klow;   // A is lower triangular: tile row i0 sums k < i0 + 64 only
+  int klow;   // A is lower triangular: tile row i0 sums k < i0 + 32 only
+  // a batch of `batch` products (0 = one) at these element strides; m_last: rows of the last one
+  // when it is narrower (else 0); kd_is_m: its k range shrinks with its rows
+  int batch;
+  int64_t a_sz, b_sz, c_sz, m_last;
+  int kd_is_m;
 };
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+// 16 x 16 x 4 product update: lane l holds row (column) l % 16 and k = l / 16 of A (B); the result's
+// lane l holds column l % 16 and rows l / 16 + 4 i.  Each element's four products are added in
+// ascending k, each with one rounding (a chain of fused multiply-adds; checked on the card).
+__device__ __forceinline__ v4d mfma_f64(double a, double b, v4d c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+#else
+  return c;
+#endif
+}
+
+// 32 x 32 tiles, each of 4 waves a 16 x 16 quarter (one chain of instructions); k in chunks of
+// 32 through LDS, the next chunk's loads in flight while one is multiplied.  Several workgroups
+// share a compute unit and cover each other's chains.
+constexpr int kDT = 32;  // tile edge
 template <typename TA, typename TB>
 __global__ __launch_bounds__(256) void dprod_kernel(DProd p) {
-  constexpr int T = 64, KC = 16;
-  __shared__ double as[KC][T + 1];
-  __shared__ double bs[KC][T + 1];
-  const int ti = blockIdx.y, tj = blockIdx.x;
-  if ((p.lower || p.mirror) && tj > ti) return;
-  const int tid = threadIdx.x;
-  const int ty = tid / 16, tx = tid % 16;
+  constexpr int T = kDT, KC = 32, PER = T * KC / 256;
+  __shared__ double as[KC][T + 2];
+  __shared__ double bs[KC][T + 2];
+  const int ti = blockIdx.y, tj = blockIdx.x, z = blockIdx.z;
+  const int64_t m = p.m_last && z == (int)gridDim.z - 1 ? p.m_last : p.m;
+  const int64_t kd = p.kd_is_m ? m : p.kd;
   const int64_t i0 = (int64_t)ti * T, j0 = (int64_t)tj * T;
-  const TA *A = reinterpret_cast<const TA *>(p.a);
-  const TB *Bm = reinterpret_cast<const TB *>(p.b);
-  double acc[4][4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[r][c] = 0.0;
+  if (i0 >= m) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wi = (wave >> 1) * 16, wj = (wave & 1) * 16, l16 = lane & 15, l4 = lane >> 4;
+  const TA *A = reinterpret_cast<const TA *>(p.a) + z * p.a_sz;
+  const TB *Bm = reinterpret_cast<const TB *>(p.b) + z * p.b_sz;
+  double *C = p.c + z * p.c_sz;
+  v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
   const bool a_krun = p.a_sk == 1;  // consecutive lanes along k when k is the contiguous index
   const bool b_jrun = p.b_sj == 1;
-  const int64_t kend = p.klow && i0 + T < p.kd ? i0 + T : p.kd;
-  for (int64_t k0 = p.kskip ? j0 : 0; k0 < kend; k0 += KC) {
-    __syncthreads();
+  const int64_t kend = p.klow && i0 + T < kd ? i0 + T : kd;
+  double va[PER], vb[PER];
+  auto fetch = [&](int64_t k0) {
 #pragma unroll
-    for (int u = 0; u < (T * KC) / 256; ++u) {
+    for (int u = 0; u < PER; ++u) {
       const int e = tid + 256 * u;
-      const int ii = a_krun ? e / KC : e % T, kk = a_krun ? e % KC : e / T;
-      const int64_t gi = i0 + ii, gk = k0 + kk;
-      as[kk][ii] = (gi < p.m && gk < p.kd) ? (double)A[gi * p.a_si + gk * p.a_sk] : 0.0;
-      const int jj = b_jrun ? e % T : e / KC, kb = b_jrun ? e / T : e % KC;
-      const int64_t gj = j0 + jj, gkb = k0 + kb;
-      bs[kb][jj] = (gj < p.n && gkb < p.kd) ? (double)Bm[gkb * p.b_sk + gj * p.b_sj] : 0.0;
+      const int64_t gi = i0 + (a_krun ? e / KC : e % T), gk = k0 + (a_krun ? e % KC : e / T);
+      const int64_t gj = j0 + (b_jrun ? e % T : e / KC), gkb = k0 + (b_jrun ? e / T : e % KC);
+      va[u] = gi < m && gk < kend ? (double)A[gi * p.a_si + gk * p.a_sk] : 0.0;
+      vb[u] = gj < p.n && gkb < kend ? (double)Bm[gkb * p.b_sk + gj * p.b_sj] : 0.0;
+    }
+  };
+  const int64_t kbeg = p.kskip ? j0 : 0;
+  if (kbeg < kend) fetch(kbeg);
+  for (int64_t k0 = kbeg; k0 < kend; k0 += KC) {
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + 256 * u;
+      as[a_krun ? e % KC : e / T][a_krun ? e / KC : e % T] = va[u];
+      bs[b_jrun ? e / T : e % KC][b_jrun ? e % T : e / KC] = vb[u];
     }
     __syncthreads();
-    const int kn = (int)(kend - k0 < KC ? kend - k0 : KC);
-    for (int k = 0; k < kn; ++k) {
-      double av[4], bv[4];
+    if (k0 + KC < kend) fetch(k0 + KC);
+    // entries past kend are zeros: they add nothing
 #pragma unroll
-      for (int r = 0; r < 4; ++r) av[r] = as[k][ty * 4 + r];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) bv[c] = bs[k][tx * 4 + c];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = __builtin_fma(av[r], bv[c], acc[r][c]);
-    }
+    for (int k = 0; k < KC; k += 4) acc = mfma_f64(as[k + l4][wi + l16], bs[k + l4][wj + l16], acc);
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int64_t gi = i0 + ty * 4 + r;
-    if (gi >= p.m) continue;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int64_t gj = j0 + tx * 4 + c;
-      if (gj >= p.n || (p.lower && gj > gi) || (p.mirror && gj > gi)) continue;
-      double *dst = p.c + gi * p.ldc + gj;
-      double v;
-      switch (p.mode) {
-        case kSub: v = *dst - acc[r][c]; break;
-        case kAdd: v = *dst + acc[r][c]; break;
-        case kSetNeg: v = -acc[r][c]; break;
-        default: v = acc[r][c]; break;
-      }
-      *dst = v;
-      if (p.mirror && gj != gi) p.c[gj * p.ldc + gi] = v;
+  for (int q = 0; q < 4; ++q) {
+    const int64_t gi = i0 + wi + 4 * q + l4, gj = j0 + wj + l16;
+    if (gi >= m || gj >= p.n) continue;
+    double *dst = C + gi * p.ldc + gj;
+    switch (p.mode) {
+      case kSub: *dst = *dst - acc[q]; break;
+      case kSetNeg: *dst = -acc[q]; break;
+      default: *dst = acc[q]; break;
     }
   }
 }
@@ -170,15 +185,92 @@ __global__ __launch_bounds__(256) void dprod_kernel(DProd p) {
 template <typename TA, typename TB>
 static hipError_t dprod(const DProd &p, hipStream_t s) {
   if (p.m <= 0 || p.n <= 0) return hipSuccess;
-  const int64_t tm = (p.m + 63) / 64, tn = (p.n + 63) / 64;
+  const int64_t tm = (p.m + kDT - 1) / kDT, tn = (p.n + kDT - 1) / kDT;
   if (tm > 65535 || tn > 2147483647) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((dprod_kernel<TA, TB>), dim3((unsigned)tn, (unsigned)tm), dim3(256), 0, s, p);
+  hipLaunchKernelGGL((dprod_kernel<TA, TB>), dim3((unsigned)tn, (unsigned)tm, (unsigned)(p.batch > 0 ? p.batch : 1)), dim3(256),
+                     0, s, p);
   return hipGetLastError();
 }
 
 __global__ __launch_bounds__(256) void fill_kernel(double *d, int64_t n, double v) {
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (e < n) d[e] = v;
+}
+
+// G[i][j] (+)= sum_t z[t][i] z[t][j], lower 32 x 32 tiles mirrored.  The 4 waves of a workgroup take
+// every fourth group of 32 tokens, operands straight from z into registers (fp32, widened exactly),
+// and add up in wave order.  K = 1024, T = 2048: 528 tiles, two waves per SIMD.
+__global__ __launch_bounds__(256) void second_moment_kernel(const float *z, int64_t ldz, int64_t T, int K, double *G,
+                                                            int accumulate) {
+  __shared__ double part[3][32][33];
+  const int ti = blockIdx.y, tj = blockIdx.x;
+  if (tj > ti) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
+  const float *zi = z + ti * 32 + l16, *zj = z + tj * 32 + l16;
+  v4d acc[2][2];
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) acc[r][c] = v4d{0.0, 0.0, 0.0, 0.0};
+  float a[8][2], b[8][2];
+  auto fetch = [&](int64_t t0) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int64_t t = t0 + 4 * q + l4;
+      const bool in = t < T;
+      const int64_t o = (in ? t : T - 1) * ldz;
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const float x = zi[o + 16 * r], y = zj[o + 16 * r];
+        a[q][r] = in ? x : 0.0f;
+        b[q][r] = in ? y : 0.0f;
+      }
+    }
+  };
+  const int64_t groups = (T + 31) / 32;
+  if (wave < groups) fetch((int64_t)wave * 32);
+  for (int64_t g = wave; g < groups; g += 4) {
+    float ca[8][2], cb[8][2];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        ca[q][r] = a[q][r];
+        cb[q][r] = b[q][r];
+      }
+    if (g + 4 < groups) fetch((g + 4) * 32);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[r][c] = mfma_f64((double)ca[q][r], (double)cb[q][c], acc[r][c]);
+  }
+  if (wave > 0)
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) part[wave - 1][16 * r + 4 * q + l4][16 * c + l16] = acc[r][c][q];
+  __syncthreads();
+  if (wave > 0) return;
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int li = 16 * r + 4 * q + l4, lj = 16 * c + l16;
+        const int64_t i = ti * 32 + li, j = tj * 32 + lj;
+        if (j > i) continue;
+        double v = acc[r][c][q] + part[0][li][lj];
+        v += part[1][li][lj];
+        v += part[2][li][lj];
+        if (accumulate) v += G[i * K + j];
+        G[i * K + j] = v;
+        if (i != j) G[j * K + i] = v;
+      }
 }
 
 hipError_t launch_gptq_hessian(const float *z, int64_t ldz, int64_t T, int K, double *G, bool accumulate,
@@ -189,23 +281,9 @@ hipError_t launch_gptq_hessian(const float *z, int64_t ldz, int64_t T, int K, do
     hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, G, n, 0.0);
     return hipGetLastError();
   }
-  // G[i][j] (+)= sum_t z[t][i] z[t][j]: A[i][t] = z[t][i], B[t][j] = z[t][j]; lower tiles,
-  // mirrored
-  DProd p{};
-  p.a = z;
-  p.a_si = 1;
-  p.a_sk = ldz;
-  p.b = z;
-  p.b_sk = ldz;
-  p.b_sj = 1;
-  p.c = G;
-  p.ldc = K;
-  p.m = K;
-  p.n = K;
-  p.kd = T;
-  p.mode = accumulate ? kAdd : kSet;
-  p.mirror = 1;
-  return dprod<float, float>(p, s);
+  const unsigned t = (unsigned)(K / 32);
+  hipLaunchKernelGGL(second_moment_kernel, dim3(t, t), dim3(256), 0, s, z, ldz, T, K, G, accumulate ? 1 : 0);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------
@@ -244,85 +322,205 @@ __global__ __launch_bounds__(256) void reverse_kernel(const double *G, int K, co
 
 constexpr int kNb = 64;  // Cholesky / inverse block
 
-// The three small dense kernels of the factor run one wave per 64 x 64 block, each lane
-// holding one row (or column) of 64 doubles in registers, every loop fully unrolled so the
-// register indices are static; the entries other lanes need go through LDS.
-
-// Cholesky of the diagonal block at k0 (lower), right-looking: lane i holds row i.  At step
-// j every lane publishes its entry j, reads the pivot d = sqrt(l_jj) and 1/d, and takes
-// column j's scaled entries l_cj = l_cj * (1/d) from LDS (the same product its owner forms),
-// then updates its entries j < c <= i.  Selects, no divergent branches.  The block's upper
-// part is written as zeros.
-__global__ __launch_bounds__(64) void potrf_block_kernel(double *A, int K, int k0) {
-  __shared__ double col[kNb];
-  const int i = threadIdx.x;
-  double r[kNb];
-  const double *src = A + (int64_t)(k0 + i) * K + k0;
+// Factor and inverse of a 64 x 64 diagonal block in LDS (row stride kLd), by a workgroup of 512
+// threads in four 16-wide steps: one wave factors the step's 16 columns with each lane holding
+// its row of them in registers (the pivot row's values through scalar registers, 1 / sqrt of the
+// pivot by two Newton steps on the hardware estimate, exact at 1), then the waves update the
+// rest; the inverse follows from the 16-wide diagonal blocks' inverses (16-wide products on the
+// matrix instruction).  a: the block (lower part), becomes L with zeros above; x: becomes L^-1.
+// One wave's chain of 64 pivots bounds it (about 0.25 us each); the former wave-per-block
+// factor and the row-parallel solves with fp64 divisions took 83 us a block.
+constexpr int kLd = kNb + 1;
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// c + f S B over 16 channels by one wave: S = s[r0 + ..][c0 + ..], B = b[k0 + k][j0 + j], or with TR
+// its transpose b[k0 + j][j0 + k]; the result in the matrix instruction's layout.
+template <bool TR>
+__device__ __forceinline__ v4d block16(const double *s, int r0, int c0, const double *b, int k0, int j0, v4d c, double f) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+  double av[4], bv[4];
 #pragma unroll
-  for (int c = 0; c < kNb; ++c) r[c] = src[c];
+  for (int q = 0; q < 4; ++q) {
+    av[q] = f * s[(r0 + l16) * kLd + c0 + 4 * q + l4];
+    bv[q] = TR ? b[(k0 + l16) * kLd + j0 + 4 * q + l4] : b[(k0 + 4 * q + l4) * kLd + j0 + l16];
+  }
 #pragma unroll
-  for (int j = 0; j < kNb; ++j) {
-    col[i] = r[j];
+  for (int q = 0; q < 4; ++q) c = mfma_f64(av[q], bv[q], c);
+  return c;
+}
+__device__ __forceinline__ void put16(double *d, int r0, int c0, v4d v) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) d[(r0 + 4 * q + l4) * kLd + c0 + l16] = v[q];
+}
+// orders a wave's LDS writes before its later reads of other lanes' values
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  lgkm_wait_all();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ void factor_block(double *a, double *x) {
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, l4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ double rdiag[kNb];
+  for (int e = tid; e < kNb * kNb; e += 512) x[(e / kNb) * kLd + e % kNb] = 0.0;
+  __syncthreads();
+  for (int o = 0; o < kNb; o += 16) {
+    const int nb = (kNb - o - 16) / 16;
+    if (wave == 0) {
+      double r[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) r[c] = a[lane * kLd + o + c];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const double d = lane_value(r[j], o + j);
+        double y = __builtin_amdgcn_rsq(d);
+        y = __builtin_fma(0.5 * y, __builtin_fma(-d * y, y, 1.0), y);
+        y = __builtin_fma(0.5 * y, __builtin_fma(-d * y, y, 1.0), y);
+        if (lane == 0) rdiag[o + j] = y;  // 1 / l_jj
+        r[j] = r[j] * y;
+#pragma unroll
+        for (int c = j + 1; c < 16; ++c) r[c] = __builtin_fma(-r[j], lane_value(r[j], o + c), r[c]);
+      }
+#pragma unroll
+      for (int c = 0; c < 16; ++c) a[lane * kLd + o + c] = o + c <= lane ? r[c] : 0.0;
+    }
     __syncthreads();
-    const double d = sqrt(col[j]);
-    const double inv = 1.0 / d;
-    r[j] = i > j ? r[j] * inv : (i == j ? d : r[j]);
+    // the rest: lower blocks (i, j) of nb x nb
+    for (int e = wave; e < nb * (nb + 1) / 2; e += 8) {
+      const int i = e >= 3 ? 2 : (e >= 1 ? 1 : 0), j = e - i * (i + 1) / 2;
+      const int r0 = o + 16 + 16 * i, c0 = o + 16 + 16 * j;
+      v4d v;
 #pragma unroll
-    for (int c = j + 1; c < kNb; ++c) {
-      const double lc = col[c] * inv;
-      r[c] = c <= i ? r[c] - r[j] * lc : r[c];
-      if ((c & 7) == 7) __builtin_amdgcn_sched_barrier(0);  // few LDS values live at a time
+      for (int q = 0; q < 4; ++q) v[q] = a[(r0 + 4 * q + l4) * kLd + c0 + l16];
+      v = block16<true>(a, r0, o, a, c0, o, v, -1.0);
+      put16(a, r0, c0, v);
     }
     __syncthreads();
   }
-  double *dst = A + (int64_t)(k0 + i) * K + k0;
+  // inverses of the 16-wide diagonal blocks, one wave each: lane i holds column i % 16,
+  // x_m = (e_m - sum_{t < m} l_mt x_t) / l_mm
+  if (wave < 4) {
+    const int o = 16 * wave, i = l16;
+    double r[16], xi[16];
 #pragma unroll
-  for (int c = 0; c < kNb; ++c) dst[c] = c <= i ? r[c] : 0.0;
+    for (int c = 0; c < 16; ++c) r[c] = a[(o + i) * kLd + o + c];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      double t = m == i ? 1.0 : 0.0;
+#pragma unroll
+      for (int q = 0; q < m; ++q) t = __builtin_fma(-xi[q], lane_value(r[q], m), t);
+      xi[m] = t * rdiag[o + m];
+    }
+    if (lane < 16)
+#pragma unroll
+      for (int m = 0; m < 16; ++m) x[(o + m) * kLd + o + i] = m >= i ? xi[m] : 0.0;
+  }
+  __syncthreads();
+  // X_ij = -X_ii sum_{j <= m < i} L_im X_mj for the 16-wide blocks, by distance from the diagonal,
+  // one wave per block; the sum goes where the result will be, then the product replaces it
+  for (int d = 1; d < 4; ++d) {
+    if (wave < 4 - d) {
+      const int i = (wave + d) * 16, j = wave * 16;
+      v4d t = v4d{0.0, 0.0, 0.0, 0.0};
+      for (int m = j; m < i; m += 16) t = block16<false>(a, i, m, x, m, j, t, 1.0);
+      put16(x, i, j, t);
+      wave_lds_fence();
+      t = block16<false>(x, i, i, x, i, j, v4d{0.0, 0.0, 0.0, 0.0}, -1.0);
+      wave_lds_fence();
+      put16(x, i, j, t);
+    }
+    __syncthreads();
+  }
 }
 
-// Rows i >= k0 + 64 of the panel: x L_kk^T = a, one lane per row (64 per workgroup), the
-// row in registers: x_c = x_c / l_cc, then x_c' -= x_c l_c'c for the later c' (each entry's
-// subtractions in ascending c, the same arithmetic as the dot-product form).
-__global__ __launch_bounds__(64) void trsm_rows_kernel(double *A, int K, int k0) {
-  __shared__ double l[kNb][kNb];  // read at wave-uniform indices only
-  const int tid = threadIdx.x;
-  for (int e = tid; e < kNb * kNb; e += 64) l[e / kNb][e % kNb] = A[(int64_t)(k0 + e / kNb) * K + k0 + e % kNb];
-  const int64_t row = (int64_t)k0 + kNb + (int64_t)blockIdx.x * 64 + tid;
-  const int64_t rr = row < K ? row : K - 1;  // lanes past the end solve a copy of the last row, unstored
-  double x[kNb];
-#pragma unroll
-  for (int c = 0; c < kNb; ++c) x[c] = A[rr * K + k0 + c];
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < kNb; ++c) {
-    x[c] = x[c] / l[c][c];
-#pragma unroll
-    for (int c2 = c + 1; c2 < kNb; ++c2) x[c2] = x[c2] - x[c] * l[c2][c];
-  }
-  if (row < K)
-#pragma unroll
-    for (int c = 0; c < kNb; ++c) A[row * K + k0 + c] = x[c];
+__device__ __forceinline__ void store_block(double *dst, int64_t ld, const double *src) {
+  for (int e = threadIdx.x; e < kNb * kNb; e += 512) dst[(e / kNb) * ld + e % kNb] = src[(e / kNb) * kLd + e % kNb];
 }
 
-// X_ii = L_ii^-1 for every diagonal block (grid = K / 64): lane c computes column c,
-// x = e_c, then x_m = x_m / l_mm and x_r -= l_rm x_m for r > m, m ascending.
-__global__ __launch_bounds__(64) void triinv_block_kernel(const double *A, int K, double *X) {
-  __shared__ double l[kNb][kNb];  // read at wave-uniform indices only
-  const int c = threadIdx.x;
-  const int k0 = blockIdx.x * kNb;
-  for (int e = c; e < kNb * kNb; e += 64) l[e / kNb][e % kNb] = A[(int64_t)(k0 + e / kNb) * K + k0 + e % kNb];
+// The first diagonal block: L_00 into A, its inverse into X.
+__global__ __launch_bounds__(512) void chol_first_kernel(double *A, int K, double *X) {
+  extern __shared__ double sm[];
+  double *a = sm, *x = sm + kNb * kLd;
+  for (int e = threadIdx.x; e < kNb * kNb; e += 512) a[(e / kNb) * kLd + e % kNb] = A[(int64_t)(e / kNb) * K + e % kNb];
   __syncthreads();
-  double x[kNb];
-#pragma unroll
-  for (int r = 0; r < kNb; ++r) x[r] = r == c ? 1.0 : 0.0;
-#pragma unroll
-  for (int m = 0; m < kNb; ++m) {
-    x[m] = x[m] / l[m][m];
-#pragma unroll
-    for (int r = m + 1; r < kNb; ++r) x[r] = x[r] - l[r][m] * x[m];
+  factor_block(a, x);
+  store_block(A, K, a);
+  store_block(X, K, x);
+}
+
+// One 64-wide step of the Cholesky factor after its diagonal block (k0): workgroup (ti, tj), ti >=
+// tj, forms the panel blocks L_i = A_i X_kk^T and L_j it needs itself (the panel is read where it
+// was, below the diagonal, and its factor goes to the transposed place above it, so no
+// workgroup waits for another) and updates its tile of the trailing matrix; workgroup (0, 0),
+// whose tile is the next diagonal block, goes on to factor and invert it.
+__global__ __launch_bounds__(512) void chol_step_kernel(double *A, int K, double *X, int k0) {
+  extern __shared__ double sm[];
+  double *s0 = sm, *s1 = sm + kNb * kLd, *s2 = sm + 2 * kNb * kLd;
+  const int ti = blockIdx.y, tj = blockIdx.x;
+  if (tj > ti) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wi = (wave >> 2) * 32, wj = (wave & 3) * 16, l16 = lane & 15, l4 = lane >> 4;
+  const int64_t ri = k0 + kNb + (int64_t)ti * kNb, rj = k0 + kNb + (int64_t)tj * kNb;
+  for (int e = tid; e < kNb * kNb; e += 512) {
+    const int r = e / kNb, c = e % kNb;
+    s0[r * kLd + c] = A[(ri + r) * K + k0 + c];
+    if (ti != tj) s1[r * kLd + c] = A[(rj + r) * K + k0 + c];
+    s2[r * kLd + c] = X[(int64_t)(k0 + r) * K + k0 + c];
   }
+  double old[2][4];
 #pragma unroll
-  for (int r = 0; r < kNb; ++r) X[(int64_t)(k0 + r) * K + k0 + c] = x[r];
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) old[r][q] = A[(ri + wi + 16 * r + 4 * q + l4) * K + rj + wj + l16];
+  __syncthreads();
+  // C (32 x 16 per wave) = S T^T over the first kn channels
+  auto product = [&](const double *S, const double *Tt, int kn, v4d (&acc)[2]) {
+    acc[0] = acc[1] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int k = 0; k < kn; k += 4) {
+      const double bv = Tt[(wj + l16) * kLd + k + l4];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) acc[r] = mfma_f64(S[(wi + 16 * r + l16) * kLd + k + l4], bv, acc[r]);
+    }
+  };
+  auto put = [&](double *S, const v4d (&v)[2]) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) S[(wi + 16 * r + 4 * q + l4) * kLd + wj + l16] = v[r][q];
+  };
+  v4d li[2], lj[2], up[2];
+  product(s0, s2, wj + 16, li);  // X_kk is lower triangular
+  if (ti != tj) product(s1, s2, wj + 16, lj);
+  __syncthreads();
+  put(s0, li);
+  if (ti != tj) put(s1, lj);
+  __syncthreads();
+  if (tj == 0)  // L_i^T above the diagonal
+    for (int e = tid; e < kNb * kNb; e += 512) {
+      const int c = e / kNb, r = e % kNb;
+      A[(int64_t)(k0 + c) * K + ri + r] = s0[r * kLd + c];
+    }
+  product(s0, ti != tj ? s1 : s0, kNb, up);
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int gr = wi + 16 * r + 4 * q + l4, gc = wj + l16;
+      const double v = old[r][q] - up[r][q];
+      if (ti > 0 || tj > 0) A[(ri + gr) * K + rj + gc] = v;
+      else s2[gr * kLd + gc] = v;
+    }
+  if (ti == 0 && tj == 0) {
+    __syncthreads();
+    factor_block(s2, s0);
+    store_block(A + ri * K + ri, K, s2);
+    store_block(X + ri * K + ri, K, s0);
+  }
 }
 
 // U[i][j] = X[K-1-i][K-1-j] on and above the diagonal, 0 below.
@@ -348,70 +546,65 @@ hipError_t launch_gptq_factor(const double *G, int K, double damp, double *U, vo
   hipLaunchKernelGGL(reverse_kernel, dim3(ge), dim3(256), 0, s, G, K, lam, A, X);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // blocked Cholesky, lower: A = L L^T in place
-  for (int k0 = 0; k0 < K; k0 += kNb) {
-    hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(64), 0, s, A, K, k0);
-    const int rest = K - k0 - kNb;
-    if (rest > 0) {
-      hipLaunchKernelGGL(trsm_rows_kernel, dim3((unsigned)((rest + 63) / 64)), dim3(64), 0, s, A, K, k0);
-      DProd p{};
-      p.a = A + (int64_t)(k0 + kNb) * K + k0;  // L[i][k0 + k]
-      p.a_si = K;
-      p.a_sk = 1;
-      p.b = A + (int64_t)(k0 + kNb) * K + k0;  // B[k][j] = L[j][k0 + k]
-      p.b_sk = 1;
-      p.b_sj = K;
-      p.c = A + (int64_t)(k0 + kNb) * K + k0 + kNb;
-      p.ldc = K;
-      p.m = rest;
-      p.n = rest;
-      p.kd = kNb;
-      p.mode = kSub;
-      p.lower = 1;
-      if ((e = dprod<double, double>(p, s)) != hipSuccess) return e;
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  // blocked Cholesky A = L L^T: diagonal blocks in place, the rest of L transposed above the
+  // diagonal; X gets the diagonal blocks' inverses
+  constexpr size_t lds2 = 2 * (size_t)kNb * kLd * sizeof(double), lds3 = 3 * (size_t)kNb * kLd * sizeof(double);
+  static std::atomic<uint64_t> attr2{0}, attr3{0};
+  if ((e = allow_dynamic_lds(&chol_first_kernel, lds2, attr2)) != hipSuccess) return e;
+  if ((e = allow_dynamic_lds(&chol_step_kernel, lds3, attr3)) != hipSuccess) return e;
+  hipLaunchKernelGGL(chol_first_kernel, dim3(1), dim3(512), lds2, s, A, K, X);
+  for (int k0 = 0; k0 + kNb < K; k0 += kNb) {
+    const unsigned t = (unsigned)((K - k0) / kNb - 1);
+    hipLaunchKernelGGL(chol_step_kernel, dim3(t, t), dim3(512), lds3, s, A, K, X, k0);
   }
-  // X = L^-1: the 64-wide diagonal blocks' inverses, then pairs of neighbouring diagonal
-  // blocks merged level by level (widths 64, 128, 256, ...): for A = block 2t, C = block
-  // 2t + 1 (possibly narrower at the end) and B the part of L below A and left of C,
-  // X[C, A] = -X_C (B X_A).  Both products skip the zeros of their triangular operand.
-  hipLaunchKernelGGL(triinv_block_kernel, dim3((unsigned)(K / kNb)), dim3(64), 0, s, A, K, X);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  // X = L^-1: pairs of neighbouring diagonal blocks merged level by level (widths 64, 128,
+  // 256, ...), every pair of a level in one launch: for A = block 2t, C = block 2t + 1
+  // (possibly narrower at the end) and B the part of L below A and left of C,
+  // X[C, A] = -X_C (B X_A).  Both products skip the zeros of their triangular operand.
   for (int n = kNb; n < K; n *= 2) {
-    for (int o = 0; o + n < K; o += 2 * n) {
-      const int n2 = o + 2 * n <= K ? n : K - o - n;  // width of C
-      DProd p{};
-      p.a = A + (int64_t)(o + n) * K + o;  // B[r][k] = L[o + n + r][o + k]
-      p.a_si = K;
-      p.a_sk = 1;
-      p.b = X + (int64_t)o * K + o;  // X_A[k][j]
-      p.b_sk = K;
-      p.b_sj = 1;
-      p.c = Tm;
-      p.ldc = n;
-      p.m = n2;
-      p.n = n;
-      p.kd = n;
-      p.mode = kSet;
-      p.kskip = 1;
-      if ((e = dprod<double, double>(p, s)) != hipSuccess) return e;
-      DProd q{};
-      q.a = X + (int64_t)(o + n) * K + o + n;  // X_C[r][k]
-      q.a_si = K;
-      q.a_sk = 1;
-      q.b = Tm;  // Tm[k][j]
-      q.b_sk = n;
-      q.b_sj = 1;
-      q.c = X + (int64_t)(o + n) * K + o;
-      q.ldc = K;
-      q.m = n2;
-      q.n = n;
-      q.kd = n2;
-      q.mode = kSetNeg;
-      q.klow = 1;
-      if ((e = dprod<double, double>(q, s)) != hipSuccess) return e;
-    }
+    const int pairs = (K - n + 2 * n - 1) / (2 * n);
+    const int64_t last = (int64_t)(pairs - 1) * 2 * n + n;  // first row of the last C
+    const int64_t sz = (int64_t)2 * n * (K + 1), m_last = K - last < n ? K - last : 0;
+    DProd p{};
+    p.a = A + n;  // B[r][k] = L[n + r][k], kept at A[k][n + r]
+    p.a_si = 1;
+    p.a_sk = K;
+    p.b = X;  // X_A[k][j]
+    p.b_sk = K;
+    p.b_sj = 1;
+    p.c = Tm;
+    p.ldc = n;
+    p.m = n;
+    p.n = n;
+    p.kd = n;
+    p.mode = kSet;
+    p.kskip = 1;
+    p.batch = pairs;
+    p.a_sz = p.b_sz = sz;
+    p.c_sz = (int64_t)n * n;
+    p.m_last = m_last;
+    if ((e = dprod<double, double>(p, s)) != hipSuccess) return e;
+    DProd q{};
+    q.a = X + (int64_t)n * K + n;  // X_C[r][k]
+    q.a_si = K;
+    q.a_sk = 1;
+    q.b = Tm;  // Tm[k][j]
+    q.b_sk = n;
+    q.b_sj = 1;
+    q.c = X + (int64_t)n * K;
+    q.ldc = K;
+    q.m = n;
+    q.n = n;
+    q.kd = n;
+    q.kd_is_m = 1;
+    q.mode = kSetNeg;
+    q.klow = 1;
+    q.batch = pairs;
+    q.a_sz = q.c_sz = sz;
+    q.b_sz = (int64_t)n * n;
+    q.m_last = m_last;
+    if ((e = dprod<double, double>(q, s)) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(unreverse_kernel, dim3(ge), dim3(256), 0, s, X, K, U);
   return hipGetLastError();
@@ -421,7 +614,7 @@ hipError_t launch_gptq_factor(const double *G, int K, double damp, double *U, vo
 // sweep
 
 constexpr int kSweepBlk = 128;  // columns per lazy batch
-constexpr int kSweepRows = 4;   // rows per in-block workgroup (the column steps are latency-bound: more workgroups)
+constexpr int kSweepRows = 2;   // rows per wave of the in-block sweep
 
 // Per row: A = max |w| (fp32, exact), the fp32 scale, fp64 inv = q / A and step = A / q,
 // and the fp64 working copy.  One workgroup per row.
@@ -451,47 +644,109 @@ __global__ __launch_bounds__(256) void sweep_init_kernel(const float *w, int64_t
   }
 }
 
-// Columns [i1, i1 + 128) of 4 rows, one at a time: code, error, and the error pushed onto
-// the block's later columns; the errors go to e [N, 128] for the product update.
-__global__ __launch_bounds__(128) void sweep_block_kernel(const double *U, int64_t N, int K, int bits, int i1,
+// a / b, correctly rounded, from r = 1 / b correctly rounded: two residual corrections of a r
+// (Markstein: a quotient within an ulp and the exact residual give the rounded quotient), for b
+// far from the ends of the exponent range.
+__device__ __forceinline__ double quotient(double a, double b, double r) {
+  double q = a * r;
+  q = __builtin_fma(__builtin_fma(-q, b, a), r, q);
+  return __builtin_fma(__builtin_fma(-q, b, a), r, q);
+}
+
+// Columns [i1, i1 + 128) of 2 rows per wave, one column at a time: every lane holds columns l and
+// 64 + l of the block in registers and forms the code and error of its own column; column c's
+// error is lane c's, broadcast through scalar registers and pushed onto the later columns.  No
+// LDS and no barrier: the chain of a column is about 15 dependent fp64 operations.  The rows of U
+// are read eight columns ahead.  The errors go to e [N, 128] for the product update.
+template <int H, bool PLAIN>
+__device__ __forceinline__ void sweep_half(const double *ur, int K, int lane, double q, const double (&inv)[kSweepRows],
+                                           const double (&step)[kSweepRows], double diag, double rdiag,
+                                           double (&w)[kSweepRows][2], double (&code)[kSweepRows][2],
+                                           double (&err)[kSweepRows][2]) {
+  constexpr int PF = 8;
+  double u0[PF], u1[PF];
+  auto fetch = [&](int c) {  // rows 64 H + c .. of the block, this half's columns and the later half's
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      const double *row = ur + (int64_t)(64 * H + c + i) * K;
+      u0[i] = row[64 * H + lane];
+      u1[i] = H == 0 ? row[64 + lane] : 0.0;
+    }
+  };
+  fetch(0);
+  for (int c0 = 0; c0 < 64; c0 += PF) {
+    double v0[PF], v1[PF];
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      v0[i] = u0[i];
+      v1[i] = u1[i];
+    }
+    if (c0 + PF < 64) fetch(c0 + PF);
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      const int c = c0 + i;
+#pragma unroll
+      for (int r = 0; r < kSweepRows; ++r) {
+        double k = rint(w[r][H] * inv[r]);
+        k = k > q ? q : k;
+        k = k < -q ? -q : k;
+        const double d = w[r][H] - k * step[r];
+        const double ev = PLAIN ? d / diag : quotient(d, diag, rdiag);
+        if (lane == c) {
+          code[r][H] = k;
+          err[r][H] = ev;
+        }
+        const double eb = lane_value(ev, c);
+        const double n0 = __builtin_fma(-eb, v0[i], w[r][H]);
+        w[r][H] = lane > c ? n0 : w[r][H];
+        if constexpr (H == 0) w[r][1] = __builtin_fma(-eb, v1[i], w[r][1]);
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void sweep_block_kernel(const double *U, int64_t N, int K, int bits, int i1,
                                                           const double *rowp, double *w64, int8_t *codes,
                                                           double *e) {
-  __shared__ double wb[kSweepRows][kSweepBlk + 1];
-  __shared__ double es[kSweepRows];
-  const int tid = threadIdx.x;
-  const int64_t r0 = (int64_t)blockIdx.x * kSweepRows;
+  const int lane = threadIdx.x & 63;
+  const int64_t r0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kSweepRows;
+  if (r0 >= N) return;
   const double q = (double)((1 << (bits - 1)) - 1);
-  for (int x = tid; x < kSweepRows * kSweepBlk; x += 128) {
-    const int r = x / kSweepBlk, c = x % kSweepBlk;
-    wb[r][c] = r0 + r < N ? w64[(r0 + r) * K + i1 + c] : 0.0;
+  const double *ur = U + (int64_t)i1 * K + i1;
+  double w[kSweepRows][2], inv[kSweepRows], step[kSweepRows], code[kSweepRows][2], err[kSweepRows][2];
+#pragma unroll
+  for (int r = 0; r < kSweepRows; ++r) {
+    const int64_t row = r0 + r < N ? r0 + r : N - 1;  // a row past the end repeats the last one, unstored
+    inv[r] = rowp[2 * row];
+    step[r] = rowp[2 * row + 1];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      w[r][h] = w64[row * K + i1 + 64 * h + lane];
+      code[r][h] = err[r][h] = 0.0;
+    }
   }
-  __syncthreads();
-  for (int c = 0; c < kSweepBlk; ++c) {
-    const int64_t gc = i1 + c;
-    if (tid < kSweepRows) {
-      const int64_t row = r0 + tid;
-      double err = 0.0;
-      if (row < N) {
-        const double inv = rowp[2 * row], step = rowp[2 * row + 1];
-        double k = 0.0;
-        if (inv != 0.0) {  // a zero row keeps codes 0 and pushes no error
-          k = rint(wb[tid][c] * inv);
-          if (k > q) k = q;
-          if (k < -q) k = -q;
-          err = (wb[tid][c] - k * step) / U[gc * K + gc];
-        }
-        codes[row * K + gc] = (int8_t)k;
-        e[row * kSweepBlk + c] = err;
-      }
-      es[tid] = err;
+  const double d0 = ur[(int64_t)lane * (K + 1)], d1 = ur[(int64_t)(64 + lane) * (K + 1)];
+  // a diagonal entry near the ends of the exponent range (or not finite) divides plainly
+  auto odd = [](double d) {
+    const double m = fabs(d);
+    return !(m > 0x1p-400 && m < 0x1p400);
+  };
+  const bool plain = __any(odd(d0) || odd(d1));
+  if (plain) {
+    sweep_half<0, true>(ur, K, lane, q, inv, step, d0, 0.0, w, code, err);
+    sweep_half<1, true>(ur, K, lane, q, inv, step, d1, 0.0, w, code, err);
+  } else {
+    sweep_half<0, false>(ur, K, lane, q, inv, step, d0, 1.0 / d0, w, code, err);
+    sweep_half<1, false>(ur, K, lane, q, inv, step, d1, 1.0 / d1, w, code, err);
+  }
+#pragma unroll
+  for (int r = 0; r < kSweepRows; ++r) {
+    if (r0 + r >= N) continue;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      codes[(r0 + r) * K + i1 + 64 * h + lane] = (int8_t)code[r][h];
+      e[(r0 + r) * kSweepBlk + 64 * h + lane] = err[r][h];
     }
-    __syncthreads();
-    const int rem = kSweepBlk - 1 - c;
-    for (int x = tid; x < kSweepRows * rem; x += 128) {
-      const int r = x / rem, c2 = c + 1 + x % rem;
-      wb[r][c2] = __builtin_fma(-es[r], U[gc * K + i1 + c2], wb[r][c2]);
-    }
-    __syncthreads();
   }
 }
 
@@ -511,9 +766,9 @@ hipError_t launch_gptq_sweep(const float *w, int64_t ldw, const double *U, int64
                      rowp, w64);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  const unsigned gb = (unsigned)((N + kSweepRows - 1) / kSweepRows);
+  const unsigned gb = (unsigned)((N + 4 * kSweepRows - 1) / (4 * kSweepRows));
   for (int i1 = 0; i1 < K; i1 += kSweepBlk) {
-    hipLaunchKernelGGL(sweep_block_kernel, dim3(gb), dim3(128), 0, s, U, N, K, bits, i1, rowp, w64, codes, e);
+    hipLaunchKernelGGL(sweep_block_kernel, dim3(gb), dim3(256), 0, s, U, N, K, bits, i1, rowp, w64, codes, e);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const int i2 = i1 + kSweepBlk;
     if (i2 < K) {
