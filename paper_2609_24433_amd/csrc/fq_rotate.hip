@@ -9,7 +9,8 @@ namespace fq {
 // Stored composite rotation (Sec. III-C, the action expert's optional transform in place of
 // the block Hadamard): gather by a channel permutation, then per-block orthogonal b x b
 // matrices, as two kernels through an fp32 workspace z [M, K]:
-//   rot_transform_kernel: a workgroup takes one block and R rows.  The block's matrix goes
+//   rot_mfma_kernel: blocks of 16 channels and more, on the matrix cores (below);
+//   rot_transform_kernel: blocks of 1 to 8 channels.  A workgroup takes one block and R rows.  The block's matrix goes
 //     to LDS transposed (4 x 4 sub-blocks: coalesced 16-byte loads, 16-byte writes), the
 //     rows' gathered, pre-multiplied inputs w_j = x[perm[kb + j]] * s_inv[perm[kb + j]]
 //     transposed as well; both are XOR-swizzled so that the transposing writes are free of
@@ -203,6 +204,125 @@ __global__ __launch_bounds__(256) void rot_transform_kernel(const void *x, int64
   }
 }
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// The 4 x 4 transpose over the wave's quarters: register p of quarter h <- register h of quarter p.
+__device__ __forceinline__ float4 transpose_quarters(float4 f) {
+  const uint32_t x = __float_as_uint(f.x), y = __float_as_uint(f.y), z = __float_as_uint(f.z), w = __float_as_uint(f.w);
+  const auto xz = __builtin_amdgcn_permlane32_swap(x, z, false, false);
+  const auto yw = __builtin_amdgcn_permlane32_swap(y, w, false, false);
+  const auto lo = __builtin_amdgcn_permlane16_swap(xz[0], yw[0], false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(xz[1], yw[1], false, false);
+  return float4{__uint_as_float(lo[0]), __uint_as_float(lo[1]), __uint_as_float(hi[0]), __uint_as_float(hi[1])};
+}
+
+// Blocks of 16 channels and more, on the fp32 matrix instruction.  v_mfma_f32_16x16x4_f32 advances
+// each output by its four products in ascending k, every step a rounded fma (bit-equal to the fma
+// chain over 800 000 outputs of 128 steps, with denormals, overflow and infinities among them), so
+// chaining it over the block from +0 is the same per-output chain as above.  A workgroup takes 128
+// channels (128 / B blocks) and 16 RT rows; a wave 32 outputs of all its rows.
+//   A = the matrix rows straight from memory to registers: lane (h, i) loads Q[i][16 s + 4 h ..],
+//       and a 4 x 4 transpose over the lane quarters (four lane swaps) leaves k = 16 s + 4 p + h
+//       in register p, what instruction p of group s wants.
+//   B = the rows' gathered, pre-multiplied inputs through LDS: lanes gather along the channels of
+//       one row, so a row's lines are fetched once and hit for its other channels; a pitch of 132
+//       words puts both the writes (along channels) and the reads (16 rows by 4 channels) on
+//       distinct banks.
+// A lane ends with 4 consecutive channels of one row: one 16-byte store.  The next tile's gather
+// is in flight under the products.  M = 816, K = 2048, b = 128: 14.4 us, against 17.5 for the
+// register-tiled fma chains this replaced (bound by their LDS reads of both operands); M = 16 6.2
+// against 7.4; b = 16 9.0 against 13.5.  What is left is the gather (9 us by itself with b = 16:
+// every 2-byte input is a lane address of its own), then the products (3.4 us at the fp32 rate).
+constexpr int kRotPitch = 132;
+
+template <typename Tin, int B, int RT>
+__global__ __launch_bounds__(256) void rot_mfma_kernel(const void *x, int64_t ldx, const int32_t *perm,
+                                                       const float *blocks, const float *chan_mult,
+                                                       const float *post_mult, int64_t M, int K, int64_t tiles, float *z) {
+  constexpr int R = 16 * RT, NS = B / 16, NV = R / 2;
+  __shared__ float vt[2][R * kRotPitch];  // vt[.][r * pitch + j] = w_j of row r
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, lh = lane >> 4;
+  const int c0 = blockIdx.x * 128;
+  const int j = tid & 127, rr = tid >> 7;
+  int src = perm ? perm[c0 + j] : c0 + j;
+  // blocks is [K / B][B][B], so output channel o's matrix row starts at o * B
+  float4 q[2][NS];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      q[u][s] = *reinterpret_cast<const float4 *>(blocks + (int64_t)(c0 + 32 * wave + 16 * u + li) * B + 16 * s + 4 * lh);
+  src = min(max(src, 0), K - 1);
+  const float cm = chan_mult ? chan_mult[src] : 1.0f;
+  using Raw = typename std::conditional<sizeof(Tin) == 2, uint16_t, float>::type;
+  const int c_out = c0 + 32 * wave + 4 * lh;
+  Raw raw[NV];
+  // rows past M load row M - 1 (no branch, so every load is in flight at once) and store 0
+  auto gather = [&](int64_t t) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) raw[k] = reinterpret_cast<const Raw *>(x)[min(t * R + rr + 2 * k, M - 1) * ldx + src];
+  };
+  auto stage = [&](int64_t t, float *dst) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      float v;
+      if constexpr (sizeof(Tin) == 2)
+        v = bf16_lo(raw[k]);
+      else
+        v = raw[k];
+      dst[(rr + 2 * k) * kRotPitch + j] = t * R + rr + 2 * k < M ? (chan_mult ? v * cm : v) : 0.0f;
+    }
+  };
+  gather(blockIdx.y);
+  __builtin_amdgcn_sched_barrier(0);  // every load above issues before the first use below
+  stage(blockIdx.y, vt[0]);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int s = 0; s < NS; ++s) q[u][s] = transpose_quarters(q[u][s]);
+  int buf = 0;
+  for (int64_t t = blockIdx.y; t < tiles; t += gridDim.y, buf ^= 1) {
+    const int64_t row0 = t * R, next = t + gridDim.y;
+    __syncthreads();  // this tile is staged, and the other buffer has been read
+    if (next < tiles) gather(next);
+    __builtin_amdgcn_sched_barrier(0);  // in flight under the products
+    v4f acc[2][RT];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < RT; ++r) acc[u][r] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    const float *vr = vt[buf] + li * kRotPitch + lh;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int jb = (32 * wave + 16 * u) / B * B;  // the block's first channel among the 128
+            const float a = p == 0 ? q[u][s].x : p == 1 ? q[u][s].y : p == 2 ? q[u][s].z : q[u][s].w;
+            acc[u][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, vr[16 * r * kRotPitch + jb + 16 * s + 4 * p], acc[u][r], 0, 0, 0);
+          }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      float pm[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) pm[i] = post_mult ? post_mult[c_out + 16 * u + i] : 1.0f;
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        const int64_t row = row0 + 16 * r + li;
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = post_mult ? acc[u][r][i] * pm[i] : acc[u][r][i];
+        if (row < M) *reinterpret_cast<float4 *>(z + row * K + c_out + 16 * u) = float4{v[0], v[1], v[2], v[3]};
+      }
+    }
+    if (next < tiles) stage(next, vt[buf ^ 1]);
+  }
+}
+
 // One workgroup per row; thread t owns 16-channel chunks t, t + 256, ... (K <= 32768).
 template <int CPT>
 __global__ __launch_bounds__(256) void rot_quant_kernel(const float *z, int64_t M, int K, int bits, float clip_ratio,
@@ -277,9 +397,8 @@ static hipError_t launch_rot_tr(const void *x, int64_t ldx, const int32_t *perm,
   return hipGetLastError();
 }
 
-// Four rows per thread when that still gives a grid of at least one workgroup per compute
-// unit (with b = 128 two such workgroups fill a compute unit's LDS), else one (small M:
-// more workgroups, each loading its block's matrix once).
+// Blocks of 1 to 8 channels: four rows per thread when that still gives a grid of at least one
+// workgroup per compute unit, else one (small M: more workgroups).
 template <typename Tin, int B>
 static hipError_t launch_rot_b(const void *x, int64_t ldx, const int32_t *perm, const float *blocks,
                                const float *chan_mult, const float *post_mult, int64_t M, int K, float *z,
@@ -287,6 +406,31 @@ static hipError_t launch_rot_b(const void *x, int64_t ldx, const int32_t *perm, 
   const int64_t wide = (K / B) * ((M + rot_rows<B, 4>() - 1) / rot_rows<B, 4>());
   return wide >= 256 ? launch_rot_tr<Tin, B, 4>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s)
                      : launch_rot_tr<Tin, B, 1>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
+}
+
+template <typename Tin, int B, int RT>
+static hipError_t launch_rot_rt(const void *x, int64_t ldx, const int32_t *perm, const float *blocks,
+                                const float *chan_mult, const float *post_mult, int64_t M, int K, float *z,
+                                hipStream_t s) {
+  const int64_t tiles = (M + 16 * RT - 1) / (16 * RT);
+  const int64_t most = K / 128 < 512 ? 512 / (K / 128) : 1;
+  hipLaunchKernelGGL((rot_mfma_kernel<Tin, B, RT>), dim3((unsigned)(K / 128), (unsigned)(RT == 1 || tiles < most ? tiles : most)),
+                     dim3(256), 0, s, x, ldx, perm, blocks, chan_mult, post_mult, M, K, tiles, z);
+  return hipGetLastError();
+}
+
+// 32 rows at a time, in at most two workgroups per compute unit that walk over the rows (each
+// matrix row is loaded once a workgroup), when the grid of such tiles is well over one per
+// compute unit; else 16 rows, one tile per workgroup.  At the line, b = 64: 352 tiles of 32 rows
+// (M 333, K 4096) 12.6 us against 10.3 in tiles of 16; 416 (M 816, K 2048) 11.7 against 12.0, and
+// 14.4 against 16.0 at b = 128.
+template <typename Tin, int B>
+static hipError_t launch_rot_m(const void *x, int64_t ldx, const int32_t *perm, const float *blocks,
+                               const float *chan_mult, const float *post_mult, int64_t M, int K, float *z,
+                               hipStream_t s) {
+  if ((M + 4096 / B - 1) / (4096 / B) > 65535) return hipErrorInvalidValue;  // the range this entry takes
+  return (K / 128) * ((M + 31) / 32) > 384 ? launch_rot_rt<Tin, B, 2>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s)
+                                           : launch_rot_rt<Tin, B, 1>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
 }
 
 template <typename Tin>
@@ -298,10 +442,10 @@ static hipError_t launch_rot_t(const void *x, int64_t ldx, const int32_t *perm, 
     case 2: return launch_rot_b<Tin, 2>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
     case 4: return launch_rot_b<Tin, 4>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
     case 8: return launch_rot_b<Tin, 8>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
-    case 16: return launch_rot_b<Tin, 16>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
-    case 32: return launch_rot_b<Tin, 32>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
-    case 64: return launch_rot_b<Tin, 64>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
-    case 128: return launch_rot_b<Tin, 128>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
+    case 16: return launch_rot_m<Tin, 16>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
+    case 32: return launch_rot_m<Tin, 32>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
+    case 64: return launch_rot_m<Tin, 64>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
+    case 128: return launch_rot_m<Tin, 128>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
     default: return hipErrorInvalidValue;
   }
 }
