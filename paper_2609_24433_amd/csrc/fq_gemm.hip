@@ -1073,10 +1073,10 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused) {
       // matrix cores, from k-major codes), whose larger tiles move fewer operand bytes.  GEMM
       // times against the LDS-ring kernel below, cold weights, one GPU: W4A4 K 16384 -> N 2048
       // M = 4096 86 / 127 us, K 2048 -> N 8192 M = 640 16.4 / 21.2, -> N 16384 M = 333 17.4 / 21.5;
-      // W8A8 129 / 161, 21.6 / 25.4, K 2048 -> N 32768 M = 200 29 / 36.  (Split K for the
-      // W8A8 projection K 16384 -> N 2048 at M = 816, 256 workgroups: 42 + 6.7 us of epilogue
-      // against 40 + 5.2 on heavy-tailed tokens, not taken.)  With up to one tile per compute unit the LDS-ring kernel keeps more of the chip busy
-      // (W4A4 K 2048 -> N 8192 M = 512 15.3 / 15.1).
+      // W8A8 129 / 161, 21.6 / 25.4, K 2048 -> N 32768 M = 200 29 / 36.  With up to one tile per
+      // compute unit the LDS-ring kernel keeps more of the chip busy (W4A4 K 2048 -> N 8192
+      // M = 512 15.3 / 15.1), and W8A8 gains nothing from splitting K to fill the grid (K 16384 ->
+      // N 2048 M = 816: 42 + 6.7 us of epilogue against 40 + 5.2 on heavy-tailed tokens).
       pl.kind = 4;
       pl.tiles = t256;
       pl.splits = 1;
