@@ -1083,13 +1083,16 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused) {
       pl.ksteps = ktot;
       return pl;
     }
-    if (off32 && bits == 4 && fused && ktot >= 32 && (tkg <= 256 || ktot >= 64) && (tkg >= 96 || ktot < 128)) {
+    if (off32 && bits == 4 && fused && ktot >= 32 && (tkg <= 256 || ktot >= 64) &&
+        tkg >= (ktot < 64 ? 0 : ktot < 128 ? 48 : 96)) {
       // INT4, K >= 4096, at most one 128 x 64 tile per compute unit (two from K = 8192 on): the K
       // range split across a workgroup's four waves (no partial buffer, no second kernel).
       // Against the kernel below: K 4096 -> N 4096 M = 512 13.5 / 15.9 us, K 6144 -> N 1536
       // M = 816 14.5 / 20.0, K 8192 -> N 2048 M = 333 16.4 / 19.7, K 16384 -> N 2048 M = 816
-      // 27.5 / 43, M = 1600 53 / 70; K 2048 -> N 2560 M = 512 10.0 / 9.8.  A grid of fewer than
-      // 96 tiles at K >= 16384 is faster with K split over workgroups (M = 200 25.2 / 19.8).
+      // 27.5 / 43, M = 1600 53 / 70; K 2048 -> N 2560 M = 512 10.0 / 9.8.  From K = 8192 on that
+      // kernel splits K over workgroups, which a small grid gains from: below 48 tiles (K 9088 ->
+      // N 816 M = 358, 39 tiles 17.6 / 18.0, and 1.5% slower as a fused call; 48 tiles 17.4 / 18.6),
+      // below 96 from K = 16384 on (M = 200 25.2 / 19.8).
       pl.kind = 3;
       pl.tiles = tkg;
       pl.splits = 1;

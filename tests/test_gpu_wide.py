@@ -22,7 +22,9 @@ def fq():
 # tiles of 128 x 64 (512 from K = 8192 on).  Ragged last row blocks (M % 32, M % 256), ragged last
 # column tiles (N % 128, N % 64), k steps that are no multiple of 4 or 3, one k step, one row.
 SHAPES = [(129, 128, 16400), (257, 384, 11040), (1000, 1152, 4240), (2049, 640, 2064), (4095, 1664, 1040),
-          (65, 4096, 1040), (97, 4224, 2064), (333, 6272, 1552), (513, 8320, 3088), (801, 16512, 1040)]
+          (65, 4096, 1040), (97, 4224, 2064), (333, 6272, 1552), (513, 8320, 3088), (801, 16512, 1040),
+          # 39 and 48 tiles of the k groups: both sides of their rule from K = 8192 on
+          (358, 9088, 816), (358, 8192, 1024)]
 
 
 @pytest.mark.parametrize("bits", [4, 8])
