@@ -10,7 +10,8 @@
 // per-step scalar offset, so the loop carries no address arithmetic.  No operand goes through LDS.
 // The products run on the FP6 matrix cores (fq_f6.hpp).  One wave per SIMD: the issue of the widening
 // (128 operations a step, 144 on INT8 operands) and of the multiplies (28 against 64 instructions)
-// bounds it.  M = 816, K 16384 -> N 2048: 28.5 us against 31.5 on INT8 operands.
+// bounds it.  M = 816, K 16384 -> N 2048: 27.7 us against 30.4 on INT8 operands; but 32.5 against 30.2
+// at M = 896, the same grid without repeated rows in the last row tile.
 #include "fq_device.hpp"
 #include "fq_f6.hpp"
 #include "fq_launch.hpp"
@@ -71,14 +72,18 @@ __global__ __launch_bounds__(64 * kKgWaves) void gemm_kgroup_kernel(KgParams p) 
   const v8i pat = f6_row_pattern(lane);
   constexpr int NSET = kKgSets;
   v4i ra[NSET][2][TI], rb[NSET][2][TJ];
+  // the two halves of a row's 64 bytes by adjacent loads: they share cache lines, and with the other
+  // blocks' loads between them the lines were fetched again (M = 896, K 16384 -> N 2048: 32.5 us
+  // against 35.6)
   auto load = [&](v4i (&ra_)[2][TI], v4i (&rb_)[2][TJ], int ks) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < TJ; ++j) rb_[h][j] = __builtin_amdgcn_raw_buffer_load_b128(brsrc, boff[j] + h * 512u, ks * 1024u, 0);
+      for (int h = 0; h < 2; ++h) ra_[h][i] = __builtin_amdgcn_raw_buffer_load_b128(arsrc, aoff[i] + h * 32u, ks * astep, 0);
 #pragma unroll
-      for (int i = 0; i < TI; ++i) ra_[h][i] = __builtin_amdgcn_raw_buffer_load_b128(arsrc, aoff[i] + h * 32u, ks * astep, 0);
-    }
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) rb_[h][j] = __builtin_amdgcn_raw_buffer_load_b128(brsrc, boff[j] + h * 512u, ks * 1024u, 0);
   };
   auto compute = [&](const v4i (&ra_)[2][TI], const v4i (&rb_)[2][TJ]) {
 #pragma unroll
