@@ -994,6 +994,57 @@ static constexpr size_t tile_lds_bytes() {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Whether the wide-tile GEMM beats the LDS-ring one on a grid of more than one 128 x 128 tile per
+// compute unit.  It holds one workgroup per compute unit, the LDS-ring kernel two: a round is 256
+// tiles of 256 x 128 against 512 of 128 x 128, and rows past M that the larger tiles add show in its
+// rounds.  A round takes it less time, by more the longer K is, since its tiles start and end more
+// slowly.  Fused calls, cold weights, us wide / LDS ring or the ratio:
+//   as many rounds: W4A4 K 16384 -> N 2048 M = 4096 102 / 139, K 2048 -> N 16384 M = 816 33 / 40, one
+//   round K = 384 0.91 to 1.0 and K = 256 1.03 to 1.05, more rounds K = 1024 0.89 to 1.0, K = 768 and
+//   896 0.89 to 0.99 with the last round filled and 0.99 to 1.08 else; W8A8 K 2048 -> N 16384 M = 816
+//   46 / 58, one round K = 128 0.86 to 0.94, three and more K = 128 to 384 0.83 to 1.03, two K = 512
+//   0.77 to 1.02, K = 128 to 384 0.82 to 1.06 filled and 0.96 to 1.07 else;
+//   up to 6/5 as many: W4A4 K = 1408 0.96 to 0.97 and 1280 1.01, W8A8 K = 256 0.86 to 0.99;
+//   up to 4/3 as many: W4A4 K = 1792 0.98 to 0.99 and 1408 1.04, W8A8 K = 512 0.87 to 1.02 and 384
+//   0.94 to 1.05;
+//   up to 3/2 as many: W4A4 K = 3072 0.99 and 2304 1.01 to 1.06, W8A8 K = 3712 0.96 and 2944 0.93 to 1.04;
+//   twice as many (M <= 128, half of a tile's rows): K 2048 -> N 65536 M = 128 W4A4 35.3 / 29.1, W8A8
+//   48.6 / 42.9; M = 807, K 4352 -> N 9200 W4A4 50.0 / 42.0.
+// With up to one tile per compute unit the LDS-ring kernel keeps more of the chip busy (W4A4 K 2048
+// -> N 8192 M = 512 15.3 / 15.1), and W8A8 gains nothing from splitting K to fill the grid (K 16384
+// -> N 2048 M = 816: 42 + 6.7 us of epilogue against 40 + 5.2 on heavy-tailed tokens).
+static bool wide_pays(int64_t t128, int64_t t256, int ktot, int bits) {
+  const int64_t ring = (t128 + 511) / 512, wide = (t256 + 255) / 256;
+  const bool filled = wide * 256 - t256 <= 102;  // at least 60% of the last round
+  if (wide <= ring) {
+    if (bits == 8) return ktot >= 4 || wide != 2 || filled;
+    return ktot >= (wide == 1 ? 3 : filled ? 6 : 8);
+  }
+  if (5 * wide <= 6 * ring) return ktot >= (bits == 4 ? 11 : 2);
+  if (3 * wide <= 4 * ring) return ktot >= (bits == 4 ? 14 : 4);
+  return 2 * wide <= 3 * ring && ktot >= (bits == 4 ? 24 : 28);
+}
+
+// Whether the k groups (INT4, fused: the K range split across a workgroup's four waves, no partial
+// buffer, no second kernel) beat the LDS-ring kernel.  Fused calls, cold weights, us or the ratio:
+//   K 4096 to 8064, at most one 128 x 64 tile per compute unit: 0.73 to 1.0 from 4 tiles up (K 4096
+//   -> N 256 M = 65 14.0 / 16.3, K 6144 -> N 1536 M = 816 22.0 / 26.4), but 1.0 to 1.06 above 200
+//   tiles in up to 8 columns (28 and more rows of tiles); above 256 tiles 1.0 to 1.1; K 2048 -> N 2560
+//   M = 512 10.0 / 9.8.
+//   From K = 8192 on that kernel splits K over workgroups and fills the chip with 64-row tiles up to
+//   64 tiles of 128 x 128 (0.91 to 1.26 there), but not above: 65 to 128 0.75 to 0.96, 129 to 199 0.82
+//   to 0.97, 200 to 256 0.85 to 0.97 (K 8192 to 9088 0.97 to 1.10).  K 16384 -> N 2048: M = 816 39.8 /
+//   53.0, M = 1600 69.4 / 76.6.
+// With more than 46 MB of codes the small grids stay here all the same: up to 17 MB of partial sums
+// beside them would not fit the 64 MiB of fq_linear_static (M = 8000, K 16384 -> N 128 96 / 83).
+static bool kgroup_pays(int64_t M, int64_t N, int64_t K, int64_t t128, int64_t tkg) {
+  const int ktot = (int)(K / kTileK);
+  if (ktot < 32 || t128 > 256) return false;
+  if (ktot < 64) return tkg <= (N > 512 ? 256 : 200);
+  if (t128 <= 64) return M * K > (int64_t(11) << 23) && tkg >= (ktot < 128 ? 48 : 96);
+  return ktot >= 72 || t128 < 200;
+}
+
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused) {
   GemmPlan pl{};
   const int ktot = (int)(K / kTileK);
@@ -1068,31 +1119,16 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused) {
     const int64_t t256 = ((M + 255) / 256) * ((N + 127) / 128);
     // byte offsets into the codes and the weights are 32-bit in the kernels of kinds 3 and 4
     const bool off32 = M * K * bits / 8 < (int64_t(1) << 31) && N * K * bits / 8 < (int64_t(1) << 31);
-    if (off32 && (bits == 8 || fused) && t128 > 256) {
-      // More than one 128 x 128 tile per compute unit: the wide-tile kernel (INT4 on the FP6
-      // matrix cores, from k-major codes), whose larger tiles move fewer operand bytes.  GEMM
-      // times against the LDS-ring kernel below, cold weights, one GPU: W4A4 K 16384 -> N 2048
-      // M = 4096 86 / 127 us, K 2048 -> N 8192 M = 640 16.4 / 21.2, -> N 16384 M = 333 17.4 / 21.5;
-      // W8A8 129 / 161, 21.6 / 25.4, K 2048 -> N 32768 M = 200 29 / 36.  With up to one tile per
-      // compute unit the LDS-ring kernel keeps more of the chip busy (W4A4 K 2048 -> N 8192
-      // M = 512 15.3 / 15.1), and W8A8 gains nothing from splitting K to fill the grid (K 16384 ->
-      // N 2048 M = 816: 42 + 6.7 us of epilogue against 40 + 5.2 on heavy-tailed tokens).
+    // More than one 128 x 128 tile per compute unit: the wide-tile kernel (INT4 on the FP6 matrix
+    // cores, from k-major codes), whose larger tiles move fewer operand bytes; wide_pays says where.
+    if (off32 && (bits == 8 || fused) && t128 > 256 && wide_pays(t128, t256, ktot, bits)) {
       pl.kind = 4;
       pl.tiles = t256;
       pl.splits = 1;
       pl.ksteps = ktot;
       return pl;
     }
-    if (off32 && bits == 4 && fused && ktot >= 32 && (tkg <= 256 || ktot >= 64) &&
-        tkg >= (ktot < 64 ? 0 : ktot < 128 ? 48 : 96)) {
-      // INT4, K >= 4096, at most one 128 x 64 tile per compute unit (two from K = 8192 on): the K
-      // range split across a workgroup's four waves (no partial buffer, no second kernel).
-      // Against the kernel below: K 4096 -> N 4096 M = 512 13.5 / 15.9 us, K 6144 -> N 1536
-      // M = 816 14.5 / 20.0, K 8192 -> N 2048 M = 333 16.4 / 19.7, K 16384 -> N 2048 M = 816
-      // 27.5 / 43, M = 1600 53 / 70; K 2048 -> N 2560 M = 512 10.0 / 9.8.  From K = 8192 on that
-      // kernel splits K over workgroups, which a small grid gains from: below 48 tiles (K 9088 ->
-      // N 816 M = 358, 39 tiles 17.6 / 18.0, and 1.5% slower as a fused call; 48 tiles 17.4 / 18.6),
-      // below 96 from K = 16384 on (M = 200 25.2 / 19.8).
+    if (off32 && bits == 4 && fused && kgroup_pays(M, N, K, t128, tkg)) {
       pl.kind = 3;
       pl.tiles = tkg;
       pl.splits = 1;
