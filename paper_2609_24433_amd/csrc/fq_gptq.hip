@@ -182,14 +182,25 @@ __global__ __launch_bounds__(256) void dprod_kernel(DProd p) {
   }
 }
 
+// The grid's y extent holds 65535 tiles of rows (2 097 120 rows), so longer products (the sweep of
+// as many weight rows; never a batch) go out in as many launches.
 template <typename TA, typename TB>
 static hipError_t dprod(const DProd &p, hipStream_t s) {
   if (p.m <= 0 || p.n <= 0) return hipSuccess;
-  const int64_t tm = (p.m + kDT - 1) / kDT, tn = (p.n + kDT - 1) / kDT;
-  if (tm > 65535 || tn > 2147483647) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((dprod_kernel<TA, TB>), dim3((unsigned)tn, (unsigned)tm, (unsigned)(p.batch > 0 ? p.batch : 1)), dim3(256),
-                     0, s, p);
-  return hipGetLastError();
+  constexpr int64_t kRows = (int64_t)65535 * kDT;
+  const int64_t tn = (p.n + kDT - 1) / kDT;
+  if (tn > 2147483647 || (p.batch > 0 && p.m > kRows)) return hipErrorInvalidValue;
+  for (int64_t r0 = 0; r0 < p.m; r0 += kRows) {
+    DProd q = p;
+    q.a = static_cast<const TA *>(p.a) + r0 * p.a_si;
+    q.c = p.c + r0 * p.ldc;
+    q.m = p.m - r0 < kRows ? p.m - r0 : kRows;
+    hipLaunchKernelGGL((dprod_kernel<TA, TB>), dim3((unsigned)tn, (unsigned)((q.m + kDT - 1) / kDT), (unsigned)(p.batch > 0 ? p.batch : 1)),
+                       dim3(256), 0, s, q);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 __global__ __launch_bounds__(256) void fill_kernel(double *d, int64_t n, double v) {
