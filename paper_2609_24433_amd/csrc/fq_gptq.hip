@@ -753,10 +753,13 @@ __global__ __launch_bounds__(256) void sweep_block_kernel(const double *U, int64
 #pragma unroll
   for (int r = 0; r < kSweepRows; ++r) {
     if (r0 + r >= N) continue;
+    // a row of zeros, or one whose maximum is infinite, has inv = 0: codes 0 and no error, whatever
+    // the chain above made of its infinities
+    const bool none = inv[r] == 0.0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      codes[(r0 + r) * K + i1 + 64 * h + lane] = (int8_t)code[r][h];
-      e[(r0 + r) * kSweepBlk + 64 * h + lane] = err[r][h];
+      codes[(r0 + r) * K + i1 + 64 * h + lane] = none ? (int8_t)0 : (int8_t)code[r][h];
+      e[(r0 + r) * kSweepBlk + 64 * h + lane] = none ? 0.0 : err[r][h];
     }
   }
 }
