@@ -57,7 +57,7 @@ __device__ __forceinline__ uint2 pack_chunk_nibbles_biased(const uint32_t (&c)[1
   return make_uint2(w[0], w[1]);
 }
 
-// Channel held by each six-bit slot of a 16-code group, the order that spread_nibbles16 gives.
+// Channel held by each six-bit slot of a 16-code group, the order that spread16 gives.
 constexpr int kF6Channel[16] = {0, 1, 3, 4, 6, 7, 9, 10, 12, 13, 15, 8, 2, 11, 5, 14};
 
 template <int S>
@@ -66,35 +66,44 @@ __device__ __forceinline__ uint32_t lshl_add(uint32_t a, uint32_t b) {
   asm("v_lshl_add_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "i"(S), "v"(b));
   return r;
 }
+// (low half of a) << S, plus b
+template <int S>
+__device__ __forceinline__ uint32_t lshl16_add(uint32_t a, uint32_t b) {
+  static_assert(S < 16, "a 16-bit factor");
+  uint32_t r;
+  if constexpr (S <= 6)
+    asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "i"(1 << S), "v"(b));
+  else
+    asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(1 << S), "v"(b));
+  return r;
+}
 
 // 16 biased bit patterns -> 64 bits from which four operations give the codes as 16 six-bit
 // fields holding code + 8 (words f0 f1 f2, slot i at bit 6 i): the first word holds f0 and, in
 // the unused upper two bits of its fields, the upper halves of f2's fields, the second word f1
-// and the lower halves of f2's.  The patterns' upper bits (0x4B400000) are carried through the
-// shifted sums and subtracted once per word.
+// and the lower halves of f2's.  The patterns' upper halves stay out: a shift by 16 and more
+// drops them, a smaller one is a multiply-add of the lower half.  So the NaN of a bf16 token,
+// whose lower half is zero, is code -8 as in pack_chunk_nibbles_biased and leaves its
+// neighbours alone.
 __device__ __forceinline__ uint2 pack_chunk_f6(const uint32_t (&c)[16]) {
-  constexpr uint32_t B = 0x4B400000u;
-  constexpr uint32_t C0 = (B << 0) + (B << 6) + (B << 12) + (B << 18) + (B << 24) + (B << 30);
-  constexpr uint32_t C1 = (B << 4) + (B << 10) + (B << 16) + (B << 22) + (B << 28);
-  constexpr uint32_t C2 = (B << 2) + (B << 8) + (B << 14) + (B << 20) + (B << 26);
   auto k = [&](int slot) { return c[kF6Channel[slot]]; };
-  uint32_t f0 = k(0) - C0;
-  f0 = lshl_add<6>(k(1), f0);
-  f0 = lshl_add<12>(k(2), f0);
-  f0 = lshl_add<18>(k(3), f0);
+  uint32_t f0 = k(5) << 30;
   f0 = lshl_add<24>(k(4), f0);
-  f0 = lshl_add<30>(k(5), f0);
-  uint32_t f1 = __builtin_amdgcn_ubfe(k(5), 2, 2) - C1;  // slot 5 straddles the words
-  f1 = lshl_add<4>(k(6), f1);
-  f1 = lshl_add<10>(k(7), f1);
+  f0 = lshl_add<18>(k(3), f0);
+  f0 = lshl16_add<12>(k(2), f0);
+  f0 = lshl16_add<6>(k(1), f0);
+  f0 = lshl16_add<0>(k(0), f0);
+  uint32_t f1 = __builtin_amdgcn_ubfe(k(5), 2, 2);  // slot 5 straddles the words
+  f1 = lshl16_add<4>(k(6), f1);
+  f1 = lshl16_add<10>(k(7), f1);
   f1 = lshl_add<16>(k(8), f1);
   f1 = lshl_add<22>(k(9), f1);
   f1 = lshl_add<28>(k(10), f1);
-  uint32_t f2 = (k(11) << 2) - C2;
-  f2 = lshl_add<8>(k(12), f2);
-  f2 = lshl_add<14>(k(13), f2);
+  uint32_t f2 = k(15) << 26;
   f2 = lshl_add<20>(k(14), f2);
-  f2 = lshl_add<26>(k(15), f2);
+  f2 = lshl16_add<14>(k(13), f2);
+  f2 = lshl16_add<8>(k(12), f2);
+  f2 = lshl16_add<2>(k(11), f2);
   return make_uint2(f0 | (f2 & 0x30C30C30u), f1 | (f2 & 0x0C30C30Cu));
 }
 
