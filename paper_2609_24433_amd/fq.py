@@ -221,7 +221,7 @@ def gemm(a_codes: torch.Tensor, delta: torch.Tensor, w_packed: torch.Tensor, w_s
     acc = torch.empty((M, N), dtype=torch.int32, device=a_codes.device) if want_acc else None
     ws = _scratch(LIB.fq_gemm_workspace_bytes(M, N, K, bits), a_codes.device) if ws is None else ws
     fn = LIB.fq_gemm_w4a4 if bits == 4 else LIB.fq_gemm_w8a8
-    _check(fn(a_codes.data_ptr(), delta.data_ptr(), w_packed.data_ptr(), w_scale.data_ptr(), _ptr(bias), y.data_ptr(),
+    _check(fn(a_codes.data_ptr(), _ptr(delta), _ptr(w_packed), _ptr(w_scale), _ptr(bias), y.data_ptr(),
               y.stride(0) if M else N, _ptr(acc), M, N, K, _ptr(ws), 0 if ws is None else ws.numel(), _stream_handle()))
     return (y, acc) if want_acc else y
 
@@ -237,7 +237,7 @@ def linear(x: torch.Tensor, w_packed: torch.Tensor, w_scale: torch.Tensor, N: in
     y = out if out is not None else x.new_empty((M, N))
     ws = _scratch(LIB.fq_linear_workspace_bytes(M, N, K, bits), x.device) if ws is None else ws
     _check(LIB.fq_linear(x.data_ptr(), x.stride(0) if M else K, _ptr(smooth_inv), _ptr(post_inv), M, K, N, b, bits,
-                         clip_ratio, w_packed.data_ptr(), w_scale.data_ptr(), _ptr(bias), y.data_ptr(),
+                         clip_ratio, _ptr(w_packed), _ptr(w_scale), _ptr(bias), y.data_ptr(),
                          y.stride(0) if M else N, _ptr(ws), 0 if ws is None else ws.numel(), _stream_handle()))
     return y
 
@@ -253,7 +253,7 @@ def linear_static(x: torch.Tensor, w_packed: torch.Tensor, w_scale: torch.Tensor
     _check_out(out, M, N)
     y = out if out is not None else torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
     _check(LIB.fq_linear_static(x.data_ptr(), x.stride(0) if M else K, _ptr(smooth_inv), _ptr(post_inv), M, K, N, b, bits,
-                                clip_ratio, w_packed.data_ptr(), w_scale.data_ptr(), _ptr(bias), y.data_ptr(),
+                                clip_ratio, _ptr(w_packed), _ptr(w_scale), _ptr(bias), y.data_ptr(),
                                 y.stride(0) if M else N, _stream_handle()))
     return y
 
@@ -268,7 +268,7 @@ def rotate_quant(x: torch.Tensor, perm: Optional[torch.Tensor], blocks: torch.Te
     codes = torch.empty((M, code_bytes(K, bits)), dtype=torch.uint8, device=x.device)
     delta = torch.empty((M,), dtype=torch.float32, device=x.device)
     ws = workspace(LIB.fq_rotate_quant_workspace_bytes(M, K), x.device)
-    _check(LIB.fq_rotate_quant(x.data_ptr(), x.stride(0) if M else K, _ptr(perm), blocks.data_ptr(), _ptr(smooth_inv),
+    _check(LIB.fq_rotate_quant(x.data_ptr(), x.stride(0) if M else K, _ptr(perm), _ptr(blocks), _ptr(smooth_inv),
                                _ptr(post_inv), M, K, b, bits, clip_ratio, codes.data_ptr(), delta.data_ptr(),
                                ws.data_ptr(), ws.numel(), _stream_handle()))
     return codes, delta
@@ -362,7 +362,7 @@ def gemm_w4a16(x: torch.Tensor, w_packed: torch.Tensor, w_scale: torch.Tensor, N
     y = out if out is not None else torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
     acc = torch.empty((M, N), dtype=torch.float32, device=x.device) if want_acc else None
     ws = _scratch(LIB.fq_gemm_w4a16_workspace_bytes(M, N, K), x.device) if ws is None else ws
-    _check(LIB.fq_gemm_w4a16(x.data_ptr(), x.stride(0) if M else K, w_packed.data_ptr(), w_scale.data_ptr(), _ptr(bias),
+    _check(LIB.fq_gemm_w4a16(x.data_ptr(), x.stride(0) if M else K, _ptr(w_packed), _ptr(w_scale), _ptr(bias),
                              y.data_ptr(), y.stride(0) if M else N, _ptr(acc), M, N, K, _ptr(ws),
                              0 if ws is None else ws.numel(), _stream_handle()))
     return (y, acc) if want_acc else y
