@@ -234,7 +234,7 @@ def linear(x: torch.Tensor, w_packed: torch.Tensor, w_scale: torch.Tensor, N: in
     M, K = x.shape
     assert x.dtype == torch.bfloat16 and (M == 0 or x.stride(1) == 1)
     _check_out(out, M, N)
-    y = out if out is not None else x.new_empty((M, N))
+    y = out if out is not None else torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
     ws = _scratch(LIB.fq_linear_workspace_bytes(M, N, K, bits), x.device) if ws is None else ws
     _check(LIB.fq_linear(x.data_ptr(), x.stride(0) if M else K, _ptr(smooth_inv), _ptr(post_inv), M, K, N, b, bits,
                          clip_ratio, _ptr(w_packed), _ptr(w_scale), _ptr(bias), y.data_ptr(),

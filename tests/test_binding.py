@@ -33,3 +33,16 @@ def test_a_missing_tensor_is_the_librarys_null_error(call, names):
         with pytest.raises(fq.FQError) as e:
             call(t)
         assert e.value.status == 1
+
+
+def test_output_of_a_tensor_subclass_is_a_plain_tensor(monkeypatch):
+    class Sub(torch.Tensor):
+        pass
+
+    class Lib:  # accepts the call
+        fq_linear_workspace_bytes = staticmethod(lambda *a: 0)
+        fq_linear = staticmethod(lambda *a: fq.FQ_OK)
+    monkeypatch.setattr(fq, "LIB", Lib)
+    t = tensors()
+    y = fq.linear(t["x"].as_subclass(Sub), t["w"], t["sw"], N, 64, 4)
+    assert type(y) is torch.Tensor and y.shape == (M, N) and y.dtype == torch.bfloat16
