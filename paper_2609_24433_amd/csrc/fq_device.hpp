@@ -113,6 +113,12 @@ __device__ __forceinline__ float lds_read4_untracked(const void *p) {
   return v;
 }
 __device__ __forceinline__ void lgkm_wait_all() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// Orders a wave's LDS writes before its later reads of other lanes' values.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  lgkm_wait_all();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 // 16-byte global load the compiler does not track: it places no wait of its own for the
 // result, which a kernel that streams many loads into registers needs when the compiler's
 // bookkeeping would otherwise make the first use wait for every load in flight.  The

@@ -84,7 +84,7 @@ __device__ __forceinline__ void write_out(const WideParams &p, F sums, uint8_t *
         }
       }
   }
-  // the wave's own part only: its LDS writes come before its reads
+  wave_lds_fence();  // lanes read what others wrote, in the wave's own part only
   constexpr int CPR = 32 * TJ / 8;
 #pragma unroll
   for (int q = 0; q < 32 * TI * CPR / 64; ++q) {

@@ -367,12 +367,6 @@ __device__ __forceinline__ void put16(double *d, int r0, int c0, v4d v) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) d[(r0 + 4 * q + l4) * kLd + c0 + l16] = v[q];
 }
-// orders a wave's LDS writes before its later reads of other lanes' values
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  lgkm_wait_all();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 __device__ __forceinline__ void factor_block(double *a, double *x) {
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, l4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
