@@ -3,8 +3,9 @@
 // The FP6 format E2M3 holds 0, 1/8, 2/8, .. 15/8 as the bit patterns 0 .. 15, so a six-bit field
 // with code + 8 (1 .. 15 for codes -7 .. 7) in its low four bits is the number (code + 8) / 8
 // exactly.  Products are integers over 64 of at most 225, and their fp32 sums stay exact: at most
-// 225 * 32768 < 2^24 (tests cover that largest sum and random operands).  The 32 x 32 x 64 instruction measured 8.4 PFLOP/s
-// against 4.2 for INT8's 32 x 32 x 32 (small operands; the power limit halves both).  With both operands biased by 8,
+// 225 * 32768 < 2^24 (tests cover the largest sum, and long sums of mixed codes to the last unit).
+// The 32 x 32 x 64 instruction measured 8.4 PFLOP/s against 4.2 for INT8's 32 x 32 x 32 (small
+// operands; under real codes the clock falls).  With both operands biased by 8,
 //   sum a w = 64 sum (a+8)/8 (w+8)/8 - 8 sum (a+8) - 8 sum (w+8) + 64 K,
 // the sums of codes coming from 16 x 16 x 128 instructions against patterns of ones.
 #pragma once

@@ -58,10 +58,10 @@ def _a256(n):
 
 def test_plan_workspaces():
     """The workspaces pin the launch plans of the long-K W4A4 projection (K 16384 -> N 2048):
-    the k-group GEMM needs no split-K partials; the GEMM entry point feeds it a k-step-major
-    copy of the canonical codes (M = 816), the fused projection's prologue writes that
-    order itself (M = 816 .. 3072); M = 2048 and 4096 through the GEMM entry point take the
-    LDS-ring kernel unsplit."""
+    the k-group GEMM needs no split-K partials; the GEMM entry point feeds it a k-major copy of
+    the canonical codes (M = 816), the fused projection's prologue writes that order itself (M =
+    816 to 2048, and for the wide tiles 3072 and 4096); M = 2048 and 4096 through the GEMM entry
+    point take the LDS-ring kernel unsplit."""
     K, N = 16384, 2048
     assert fq.gemm_workspace_bytes(816, N, K, 4) == _a256(816 * K // 2)
     for M in (2048, 4096):

@@ -161,15 +161,15 @@ def test_down_proj_sweep(M, b, bits):
     run_and_check(x, wl.projection_weight(p), b, bits, rows=sample_rows(M, seed=M + b))
 
 
-# ------------------------------------------------------------------ k-group plan, fused path
+# ------------------------------------------------------------------ k-major codes, fused path
 
-@pytest.mark.parametrize("M,N", [(1700, 2000), (3072, 2048)])
+@pytest.mark.parametrize("M,N", [(1700, 2000), (2048, 2048), (3072, 2048)])
 def test_fused_kgroup_wide_plan_sampled(M, N):
-    """A fused projection whose prologue writes the codes k-step major takes the k-group
-    GEMM on grids of up to 1023 tiles of 128 x 64 at K = 16384, where the GEMM entry point
-    (canonical codes) keeps the LDS-ring kernel: ragged rows and columns against the oracle
-    on sampled rows, and the two outputs identical bit for bit everywhere."""
-    flush(f"full size: fused k-group plan M={M} K=16384 N={N}")
+    """A fused projection whose prologue writes the codes k major takes the k-group GEMM on grids of up
+    to 256 tiles of 128 x 128 at K = 16384 (M = 1700, 2048) and the wide-tile GEMM above that (M =
+    3072), where the GEMM entry point (canonical codes) keeps the LDS-ring kernel: ragged rows and
+    columns against the oracle on sampled rows, and the two outputs identical bit for bit everywhere."""
+    flush(f"full size: fused plan on k-major codes M={M} K=16384 N={N}")
     f = fq()
     K, b, bits = 16384, 128, 4
     x = synth.activations(M, K, seed=M, outlier_frac=0.005, outlier_scale=50.0)

@@ -4,6 +4,7 @@ bit for bit."""
 import pytest
 import torch
 
+import tests.test_gpu_wide as wide
 from paper_2609_24433_amd import synth
 from tests.gpu_util import DEV, flush
 
@@ -41,3 +42,52 @@ def test_tokens_that_are_not_finite(M, K, N, clip, value):
     for b in (1, 32):
         y, y2 = both_paths(x.to(DEV), w, b, 4, clip)
         assert torch.equal(y, y2)
+
+
+@pytest.mark.parametrize("b", [1, 32, 128, 256])
+@pytest.mark.parametrize("clip,folds", [(0.9, "both"), (0.75, "none"), (1.0, "before"), (1.0, "after")])
+@pytest.mark.parametrize("M,K,N", [
+    # the k groups and the wide tiles from every row shape of the prologue: rows that share a workgroup
+    # (K up to 4096), 256, 512 and 1024 threads a row
+    (333, 4096, 1552), (333, 6144, 1552), (801, 16384, 1552), (700, 32768, 1552), (257, 2048, 16400), (2049, 1024, 2064)])
+def test_folds_clips_and_blocks(M, K, N, b, clip, folds):
+    flush(f"major codes M={M} K={K} N={N} b={b} clip={clip} folds={folds}")
+    x = synth.activations(M, K, seed=M + b, outlier_frac=0.01, outlier_scale=30.0).to(DEV)
+    w = torch.from_numpy(synth.weights(N, K, seed=N)).to(DEV)
+    vec = lambda seed, on: torch.from_numpy(synth.channel_vector(K, seed=seed, low=0.5, high=2.0)).to(DEV) if on else None
+    y, y2 = both_paths(x, w, b, 4, clip, vec(1, folds in ("before", "both")), vec(2, folds in ("after", "both")))
+    assert torch.equal(y, y2)
+
+
+# two k steps (INT8), k steps that are 2 mod 4 (both widths)
+@pytest.mark.parametrize("M,K,N,bits", [(300, 256, 12304, 8), (2049, 768, 2064, 4), (2049, 768, 2064, 8),
+                                        (1000, 1280, 4240, 4), (1000, 1280, 4240, 8)])
+def test_wide_tiles_k_steps(M, K, N, bits):
+    wide.test_fused_equals_split(M, K, N, bits)
+
+
+@pytest.mark.parametrize("M,N", [(816, 2048), (2064, 2064)])  # the k groups, the wide tiles
+def test_long_sums_to_the_last_unit(M, N):
+    """K = 32768 of codes 5 to 7: the products' fp32 sums of (code + 8) reach 7 million with all their low
+    bits in use.  A row differs from row 0 in at most 20 codes by one, and the bias takes row 0's sum
+    off before the bf16 rounding, so what is left is an integer below 256, which bf16 holds: an error
+    of one unit in an accumulator shows."""
+    from paper_2609_24433_amd import fq
+    K = 32768
+    flush(f"long sums M={M} N={N}")
+    g = torch.Generator().manual_seed(M)
+    w = torch.randint(5, 8, (N, K), generator=g)
+    base = torch.randint(5, 8, (K,), generator=g)
+    w[:, 0] = base[0] = 7  # every row's maximum: its step is 1
+    step = torch.zeros((M, K), dtype=torch.int64)
+    at = torch.randint(1, K, (M, 20), generator=g)
+    step.scatter_(1, at, torch.where(base[at] == 7, -1, 1) * (torch.arange(20) < 10 + torch.arange(M)[:, None] % 11))
+    step[0] = 0
+    x = (base + step).to(torch.bfloat16).to(DEV)
+    wc, sw = fq.quantize_weights(w.float().to(DEV), 1, 4)
+    assert torch.equal(wc.cpu().long(), w) and bool((sw == 1).all())
+    sum0 = (w.double() @ base.double()).long()
+    y = fq.linear(x, fq.pack_weights(wc, 4), sw, N, 1, 4, bias=-sum0.float().to(DEV))
+    want = (step.double().to(DEV) @ w.double().to(DEV).t().contiguous()).long()
+    assert int(want.abs().max()) < 256 and int(sum0.max()) > 1_000_000
+    assert torch.equal(y.long(), want)

@@ -18,12 +18,13 @@ def fq():
     return _fq
 
 
-# (M, K, N): wide tiles need more than 256 tiles of 128 x 128, k groups K >= 4096 and at most 256
-# tiles of 128 x 64 (512 from K = 8192 on).  Ragged last row blocks (M % 32, M % 256), ragged last
-# column tiles (N % 128, N % 64), k steps that are no multiple of 4 or 3, one k step, one row.
+# (M, K, N): wide tiles need more than 256 tiles of 128 x 128 (INT4 3 k steps), k groups K >= 4096 and
+# at most 256 tiles of 128 x 64 (up to 256 of 128 x 128 from K = 8192 on, but more than 64).  Ragged
+# last row blocks (M % 32, M % 256), ragged last column tiles (N % 128, N % 64), k steps that are no
+# multiple of 4 or 3, one k step.
 SHAPES = [(129, 128, 16400), (257, 384, 11040), (1000, 1152, 4240), (2049, 640, 2064), (4095, 1664, 1040),
           (65, 4096, 1040), (97, 4224, 2064), (333, 6272, 1552), (513, 8320, 3088), (801, 16512, 1040),
-          # 39 and 48 tiles of the k groups: both sides of their rule from K = 8192 on
+          # grids of up to 64 tiles of 128 x 128 from K = 8192 on: the LDS-ring kernel
           (358, 9088, 816), (358, 8192, 1024)]
 
 
@@ -59,7 +60,8 @@ def test_fused_equals_split(M, K, N, bits):
 @pytest.mark.parametrize("M,N", [(816, 2048), (2064, 2064)])
 def test_largest_sums_are_exact(M, N):
     """Every code 7 at K = 32768: the six-bit fields hold 15, their products' fp32 sums reach
-    225 * 32768, and the accumulators 49 * 32768 come out exactly."""
+    225 * 32768, and the accumulators come out as 49 * 32768 to bf16's rounding (to the last unit:
+    test_gpu_major_codes.py, test_long_sums_to_the_last_unit)."""
     f = fq()
     K = 32768
     x = torch.ones((M, K), dtype=torch.bfloat16, device=DEV)
