@@ -12,25 +12,26 @@ inputs are resident in HBM when the timed region starts.  The 10-step denoising 
 captured into one HIP graph (each step also into a graph of its own, for a remainder of K)
 and the timed region runs exactly K steps.
 
-The JSON line also carries
+The JSON line (one, of a few KB: a reader that keeps the end of stdout holds it whole) also carries
   roofline   the step's longest launch, timed with cold weights (rotating copies of >= 1 GiB
              so that they come from HBM), resident weights beside it;
   graded     the graded single projections: the down-projection K 16384 -> N 2048 at
              M = 50, 816 and 4096, W4A4 and W8A8, the fused projection and its GEMM alone,
              and the backbone's gate (2048 -> 16384) and down projections at M = 816, cold;
+  cpu_baseline  the CPU oracle on the host cores (all threads, and one thread).
+Each point goes to stderr as it is measured, and the whole record to --record FILE:
   points     every other configuration: the single linear (M 64, 1024 -> 1024, b 64), the
              action-expert sites with cold and resident weights, every projection of the
              backbone layer at M = 816, the whole down-projection sweep (48 points: M in
              {1, 16, 50, 256, 816, 4096} x b in {32, 64, 128, 256} x W4A4 / W8A8), the
              prologue alone (block Hadamard against the composite rotation), weight-only
              INT4, the offline GPTQ stages, the 18-layer selective-INT8 backbone chain at
-             b = 128 and b = 1, and bf16 torch.matmul context points;
-  cpu_baseline  the CPU oracle on the host cores (all threads, and one thread).
+             b = 128 and b = 1, and bf16 torch.matmul context points.
 Each graded and point record carries `rocprof_us`, the per-call kernel time of the same
 point in the committed rocprofv3 summary (profiles/points_kernels_by_grid.json, written by
 --summarize-trace from a `--rocprof-points` trace) while its source digest matches.
 
-  python bench.py [--steps K] [--warmup W] [--no-cpu-baseline] [--no-points] [--points GROUPS]
+  python bench.py [--steps K] [--warmup W] [--no-cpu-baseline] [--no-points] [--points GROUPS] [--record FILE]
   python bench.py --rocprof-points           (under rocprofv3 --kernel-trace --stats)
   python bench.py --summarize-trace CSV --manifest STDOUT_OF_THAT_RUN
   python bench.py --traffic-site S | --counter-point P | --copy-calibration   (under rocprofv3 --pmc)
@@ -92,7 +93,16 @@ def parse():
                     help="write profiles/bench_kernel_stats.md from a --stats kernel summary of the default run and exit")
     ap.add_argument("--bench-json", default=None, help="stdout of the traced run, for --summarize-stats")
     ap.add_argument("--points", default=None, help="comma-separated point groups to run (default: all)")
+    ap.add_argument("--record", default=None, help="write the whole record (the line and every point) to this file")
     return ap.parse_args()
+
+
+def result_line(rec):
+    """The line on stdout: the record without its points (some 30 KB of them)."""
+    line = {k: v for k, v in rec.items() if k != "points"}
+    if "points" in rec:
+        line["points_measured"] = len(rec["points"])
+    return json.dumps(line)
 
 
 def log(args, msg):
@@ -1302,7 +1312,10 @@ def main():
         rec["points"] = pts
     if not args.no_cpu_baseline:
         rec["cpu_baseline"] = cpu_baseline(st, oracle, synth)
-    print(json.dumps(rec), flush=True)
+    if args.record:
+        with open(args.record, "w") as f:
+            f.write(json.dumps(rec) + "\n")
+    print(result_line(rec), flush=True)
 
 
 if __name__ == "__main__":

@@ -98,3 +98,19 @@ def test_trace_summary_splits_points_at_sentinels(tmp_path):
     man.write_text(json.dumps({"rocprof_manifest": [{"name": "p0", "calls": 3}]}) + "\n")
     with pytest.raises(SystemExit):
         bench.summarize_trace(str(csv_path), str(man), str(out))
+
+
+def test_result_line_is_short_and_whole():
+    """stdout gets one line that fits a reader's tail, with every field of the result; the points stay in
+    the record."""
+    import json
+    import os
+    with open(os.path.join(bench.PROFILES, "bench_line.json")) as f:
+        rec = json.load(f)
+    text = bench.result_line(rec)
+    line = json.loads(text)
+    assert len(text) < 12000 and "\n" not in text and "points" not in line
+    assert line["points_measured"] == len(rec["points"]) > 50
+    for key in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                "vs_baseline", "dtype", "data", "config", "roofline", "graded"):
+        assert line[key] == rec[key]
