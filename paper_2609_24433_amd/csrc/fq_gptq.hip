@@ -90,9 +90,9 @@ hipError_t launch_transform(const void *x, bool x_is_f32, int64_t ldx, const flo
 enum : int { kSub = 0, kSetNeg = 1, kSet = 2 };
 
 struct DProd {
-  const void *a;
+  const double *a;
   int64_t a_si, a_sk;  // element strides of A: rows i, k
-  const void *b;
+  const double *b;
   int64_t b_sk, b_sj;  // element strides of B: k, columns j
   double *c;
   int64_t ldc;
@@ -123,7 +123,6 @@ __device__ __forceinline__ v4d mfma_f64(double a, double b, v4d c) {
 // 32 through LDS, the next chunk's loads in flight while one is multiplied.  Several workgroups
 // share a compute unit and cover each other's chains.
 constexpr int kDT = 32;  // tile edge
-template <typename TA, typename TB>
 __global__ __launch_bounds__(256) void dprod_kernel(DProd p) {
   constexpr int T = kDT, KC = 32, PER = T * KC / 256;
   __shared__ double as[KC][T + 2];
@@ -135,8 +134,7 @@ __global__ __launch_bounds__(256) void dprod_kernel(DProd p) {
   if (i0 >= m) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wi = (wave >> 1) * 16, wj = (wave & 1) * 16, l16 = lane & 15, l4 = lane >> 4;
-  const TA *A = reinterpret_cast<const TA *>(p.a) + z * p.a_sz;
-  const TB *Bm = reinterpret_cast<const TB *>(p.b) + z * p.b_sz;
+  const double *A = p.a + z * p.a_sz, *Bm = p.b + z * p.b_sz;
   double *C = p.c + z * p.c_sz;
   v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
   const bool a_krun = p.a_sk == 1;  // consecutive lanes along k when k is the contiguous index
@@ -149,8 +147,8 @@ __global__ __launch_bounds__(256) void dprod_kernel(DProd p) {
       const int e = tid + 256 * u;
       const int64_t gi = i0 + (a_krun ? e / KC : e % T), gk = k0 + (a_krun ? e % KC : e / T);
       const int64_t gj = j0 + (b_jrun ? e % T : e / KC), gkb = k0 + (b_jrun ? e / T : e % KC);
-      va[u] = gi < m && gk < kend ? (double)A[gi * p.a_si + gk * p.a_sk] : 0.0;
-      vb[u] = gj < p.n && gkb < kend ? (double)Bm[gkb * p.b_sk + gj * p.b_sj] : 0.0;
+      va[u] = gi < m && gk < kend ? A[gi * p.a_si + gk * p.a_sk] : 0.0;
+      vb[u] = gj < p.n && gkb < kend ? Bm[gkb * p.b_sk + gj * p.b_sj] : 0.0;
     }
   };
   const int64_t kbeg = p.kskip ? j0 : 0;
@@ -184,7 +182,6 @@ __global__ __launch_bounds__(256) void dprod_kernel(DProd p) {
 
 // The grid's y extent holds 65535 tiles of rows (2 097 120 rows), so longer products (the sweep of
 // as many weight rows; never a batch) go out in as many launches.
-template <typename TA, typename TB>
 static hipError_t dprod(const DProd &p, hipStream_t s) {
   if (p.m <= 0 || p.n <= 0) return hipSuccess;
   constexpr int64_t kRows = (int64_t)65535 * kDT;
@@ -192,10 +189,10 @@ static hipError_t dprod(const DProd &p, hipStream_t s) {
   if (tn > 2147483647 || (p.batch > 0 && p.m > kRows)) return hipErrorInvalidValue;
   for (int64_t r0 = 0; r0 < p.m; r0 += kRows) {
     DProd q = p;
-    q.a = static_cast<const TA *>(p.a) + r0 * p.a_si;
+    q.a = p.a + r0 * p.a_si;
     q.c = p.c + r0 * p.ldc;
     q.m = p.m - r0 < kRows ? p.m - r0 : kRows;
-    hipLaunchKernelGGL((dprod_kernel<TA, TB>), dim3((unsigned)tn, (unsigned)((q.m + kDT - 1) / kDT), (unsigned)(p.batch > 0 ? p.batch : 1)),
+    hipLaunchKernelGGL(dprod_kernel, dim3((unsigned)tn, (unsigned)((q.m + kDT - 1) / kDT), (unsigned)(p.batch > 0 ? p.batch : 1)),
                        dim3(256), 0, s, q);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -589,7 +586,7 @@ hipError_t launch_gptq_factor(const double *G, int K, double damp, double *U, vo
     p.a_sz = p.b_sz = sz;
     p.c_sz = (int64_t)n * n;
     p.m_last = m_last;
-    if ((e = dprod<double, double>(p, s)) != hipSuccess) return e;
+    if ((e = dprod(p, s)) != hipSuccess) return e;
     DProd q{};
     q.a = X + (int64_t)n * K + n;  // X_C[r][k]
     q.a_si = K;
@@ -609,7 +606,7 @@ hipError_t launch_gptq_factor(const double *G, int K, double damp, double *U, vo
     q.a_sz = q.c_sz = sz;
     q.b_sz = (int64_t)n * n;
     q.m_last = m_last;
-    if ((e = dprod<double, double>(q, s)) != hipSuccess) return e;
+    if ((e = dprod(q, s)) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(unreverse_kernel, dim3(ge), dim3(256), 0, s, X, K, U);
   return hipGetLastError();
@@ -794,7 +791,7 @@ hipError_t launch_gptq_sweep(const float *w, int64_t ldw, const double *U, int64
       p.n = K - i2;
       p.kd = kSweepBlk;
       p.mode = kSub;
-      if ((err = dprod<double, double>(p, s)) != hipSuccess) return err;
+      if ((err = dprod(p, s)) != hipSuccess) return err;
     }
   }
   return hipSuccess;
