@@ -10,75 +10,45 @@ namespace fq {
 // the block Hadamard): gather by a channel permutation, then per-block orthogonal b x b
 // matrices, as two kernels through an fp32 workspace z [M, K]:
 //   rot_mfma_kernel: blocks of 16 channels and more, on the matrix cores (below);
-//   rot_transform_kernel: blocks of 1 to 8 channels.  A workgroup takes one block and R rows.  The block's matrix goes
-//     to LDS transposed (4 x 4 sub-blocks: coalesced 16-byte loads, 16-byte writes), the
-//     rows' gathered, pre-multiplied inputs w_j = x[perm[kb + j]] * s_inv[perm[kb + j]]
-//     transposed as well; both are XOR-swizzled so that the transposing writes are free of
-//     bank conflicts.  Thread (g, h) owns TR rows times TI outputs and, for j = 0..b-1
-//     ascending, reads TI matrix entries (one 16-byte read) and TR inputs (broadcast) and
-//     advances each output's fma chain Q[i][j] * w_j from +0: the register-tiled form of the
-//     per-output chain, whose order it keeps.  Then the optional fold-after multiplier;
+//   rot_transform_kernel: blocks of 1 to 8 channels.  A workgroup takes one block and R rows.  The
+//     block's matrix goes to LDS transposed, the rows' gathered, pre-multiplied inputs
+//     w_j = x[perm[kb + j]] * s_inv[perm[kb + j]] transposed as well and XOR-swizzled so that the
+//     transposing writes are free of bank conflicts.  Thread (g, h) owns TR rows times TI outputs
+//     and, for j = 0..b-1 ascending, reads TI matrix entries and TR inputs and advances each output's
+//     fma chain Q[i][j] * w_j from +0.  Then the optional fold-after multiplier;
 //   rot_quant_kernel: one workgroup per row: row absmax, eq. (5) with c_b = 1 (the
 //     blocks are orthonormal), canonical packing.
 // Permutation entries are clamped into [0, K): a bad permutation gives wrong codes, never
 // an out-of-bounds read.
 
-template <int B>
+template <int B, int TR>
 struct RotShape {
   static constexpr int TI = B < 4 ? B : 4;  // outputs per thread
   static constexpr int NI = B / TI;         // output groups per block
-  static constexpr int NRG = 256 / NI;      // row groups per workgroup
-  static constexpr int QSW = (B / 4 < 8 ? (B >= 4 ? B / 4 : 1) : 8) - 1;  // matrix chunk swizzle mask
+  static constexpr int R = 256 / NI * TR;   // rows per workgroup
 };
-
-template <int B, int TR>
-constexpr int rot_rows() { return RotShape<B>::NRG * TR; }
-
-template <int B, int TR>
-constexpr size_t rot_lds_bytes() {
-  return ((size_t)B * B + (size_t)B * rot_rows<B, TR>()) * sizeof(float);
-}
 
 template <typename Tin, int B, int TR>
 __global__ __launch_bounds__(256) void rot_transform_kernel(const void *x, int64_t ldx, const int32_t *perm,
                                                             const float *blocks, const float *chan_mult,
                                                             const float *post_mult, int64_t M, int K, float *z) {
-  using S = RotShape<B>;
-  constexpr int R = rot_rows<B, TR>();
+  using S = RotShape<B, TR>;
+  constexpr int TI = S::TI, R = S::R;
   // input swizzle mask; with four rows per thread it keeps each thread's rows one aligned
-  // 16-byte group (two LDS reads per j in all, few enough for the lgkm counter to track a
-  // whole prefetched group)
+  // 16-byte group
   constexpr int VSW = ((R < 32 ? R : 32) - 1) & (TR == 4 ? ~3 : ~0);
-  extern __shared__ __attribute__((aligned(16))) float rot_lds[];
-  // qt[j * B + 4 * (c ^ sw(j)) + u] = Q[4 c + u][j], sw(j) = (j / 4) & QSW
-  // vt[j * R + (r ^ (j & VSW))] = w_j of row r
-  float *qt = rot_lds;
-  float *vt = rot_lds + B * B;
+  // qt[j * B + i] = Q[i][j], vt[j * R + (r ^ (j & VSW))] = w_j of row r
+  __shared__ __attribute__((aligned(16))) float qt[B * B], vt[B * R];
   const int tid = threadIdx.x;
   const int kblk = blockIdx.x;
   const int64_t row0 = (int64_t)blockIdx.y * R;
-  const float *Q = blocks + (int64_t)kblk * B * B;
-  // Thread (rr, j) gathers channel perm[kb + j] for rows rr, rr + 256/b, ...: one
-  // permutation entry and multiplier per thread.  Loads go out in dependency order
-  // (permutation, matrix, inputs) and all before the first LDS write, so the matrix's
-  // round trip overlaps the permutation's and the gather's.
+  // Thread (rr, j) gathers channel perm[kb + j] for rows rr, rr + 256/b, ...: one permutation
+  // entry and multiplier per thread.  Every load goes out before the first LDS write, so the
+  // matrix's round trip overlaps the permutation's and the gather's.
   constexpr int JR = 256 / B, NV = R / JR;
   const int j = tid % B, rr = tid / B;
   int src = perm ? perm[kblk * B + j] : kblk * B + j;
-  constexpr int NBK = B / 4, NSB = NBK * NBK, NQ = B >= 4 ? (NSB + 255) / 256 : 1;
-  float4 tq[NQ][4];
-  if constexpr (B >= 4) {
-    // sub-block (ib, jb) = rows 4 ib.. of columns 4 jb..; lanes take consecutive jb
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-      const int sb = tid + 256 * k;
-      if (NSB % 256 == 0 || sb < NSB) {
-        const int jb = sb % NBK, ib = sb / NBK;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) tq[k][u] = *reinterpret_cast<const float4 *>(Q + (4 * ib + u) * B + 4 * jb);
-      }
-    }
-  }
+  const float qv = tid < B * B ? blocks[(int64_t)kblk * B * B + tid] : 0.0f;
   src = min(max(src, 0), K - 1);
   const float cm = chan_mult ? chan_mult[src] : 1.0f;
   // rows past M load row M - 1 (no branch, so every load is in flight at once) and store 0
@@ -90,23 +60,7 @@ __global__ __launch_bounds__(256) void rot_transform_kernel(const void *x, int64
     raw[k] = reinterpret_cast<const Raw *>(x)[row * ldx + src];
   }
   __builtin_amdgcn_sched_barrier(0);  // every load above issues before the first use below
-  if constexpr (B >= 4) {
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-      const int sb = tid + 256 * k;
-      if (NSB % 256 == 0 || sb < NSB) {
-        const int jb = sb % NBK, ib = sb / NBK;
-        const int col = 4 * (ib ^ (jb & S::QSW));
-        float *d = qt + 4 * jb * B + col;
-        *reinterpret_cast<float4 *>(d) = float4{tq[k][0].x, tq[k][1].x, tq[k][2].x, tq[k][3].x};
-        *reinterpret_cast<float4 *>(d + B) = float4{tq[k][0].y, tq[k][1].y, tq[k][2].y, tq[k][3].y};
-        *reinterpret_cast<float4 *>(d + 2 * B) = float4{tq[k][0].z, tq[k][1].z, tq[k][2].z, tq[k][3].z};
-        *reinterpret_cast<float4 *>(d + 3 * B) = float4{tq[k][0].w, tq[k][1].w, tq[k][2].w, tq[k][3].w};
-      }
-    }
-  } else {
-    if (tid < B * B) qt[(tid / B) * B + tid % B] = Q[(tid % B) * B + tid / B];
-  }
+  if (tid < B * B) qt[(tid % B) * B + tid / B] = qv;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const bool in = row0 + rr + JR * k < M;
@@ -118,87 +72,40 @@ __global__ __launch_bounds__(256) void rot_transform_kernel(const void *x, int64
     vt[j * R + ((rr + JR * k) ^ (j & VSW))] = in ? (chan_mult ? v * cm : v) : 0.0f;
   }
   __syncthreads();
-  const int h = tid % S::NI, g = tid / S::NI;
-  const int r0 = g * TR;
-  float acc[TR][S::TI];
+  const int h = tid % S::NI, r0 = tid / S::NI * TR;
+  float acc[TR][TI];
 #pragma unroll
   for (int t = 0; t < TR; ++t)
 #pragma unroll
-    for (int c = 0; c < S::TI; ++c) acc[t][c] = 0.0f;
-  if constexpr (S::TI == 4) {
-    // groups of 4 j, double-buffered in registers: group jg + 1 is read while group jg is
-    // multiplied, so LDS latency overlaps the fma chains
-    constexpr int NG = B / 4;
-    float4 qa[2][4];
-    float va[2][4][TR];
-    auto load_group = [&](int buf, int jg) {
-      const int col = 4 * (h ^ (jg & S::QSW));
+    for (int c = 0; c < TI; ++c) acc[t][c] = 0.0f;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = 4 * jg + u;
-        qa[buf][u] = *reinterpret_cast<const float4 *>(qt + j * B + col);
-        if constexpr (TR == 4) {
-          const float4 w4 = *reinterpret_cast<const float4 *>(vt + j * R + (r0 ^ (j & VSW)));
-          va[buf][u][0] = w4.x; va[buf][u][1] = w4.y; va[buf][u][2] = w4.z; va[buf][u][3] = w4.w;
-        } else {
+  for (int jj = 0; jj < B; ++jj) {
+    float q[TI], w[TR];
 #pragma unroll
-          for (int t = 0; t < TR; ++t) va[buf][u][t] = vt[j * R + ((r0 + t) ^ (j & VSW))];
-        }
-      }
-    };
-    auto fma_group = [&](int buf) {
+    for (int c = 0; c < TI; ++c) q[c] = qt[jj * B + TI * h + c];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+    for (int t = 0; t < TR; ++t) w[t] = vt[jj * R + (TR == 4 ? (r0 ^ (jj & VSW)) + t : r0 ^ (jj & VSW))];
 #pragma unroll
-        for (int t = 0; t < TR; ++t) {
-          const float w = va[buf][u][t];
-          acc[t][0] = __builtin_fmaf(qa[buf][u].x, w, acc[t][0]);
-          acc[t][1] = __builtin_fmaf(qa[buf][u].y, w, acc[t][1]);
-          acc[t][2] = __builtin_fmaf(qa[buf][u].z, w, acc[t][2]);
-          acc[t][3] = __builtin_fmaf(qa[buf][u].w, w, acc[t][3]);
-        }
-    };
-    // the reads past the last group re-read it (valid LDS, results unused): no branch in
-    // the loop, so the two register sets keep their registers instead of being copied
-    load_group(0, 0);
-#pragma unroll 1
-    for (int jg = 0; jg < NG; jg += 2) {
-      load_group(1, jg + 1 < NG ? jg + 1 : NG - 1);
-      fma_group(0);
-      load_group(0, jg + 2 < NG ? jg + 2 : NG - 1);
-      if constexpr (NG % 2 == 0) {
-        fma_group(1);
-      } else {
-        if (jg + 1 < NG) fma_group(1);
-      }
-    }
-  } else {
+    for (int t = 0; t < TR; ++t)
 #pragma unroll
-    for (int j = 0; j < B; ++j) {
-#pragma unroll
-      for (int t = 0; t < TR; ++t) {
-        const float w = vt[j * R + ((r0 + t) ^ (j & VSW))];
-#pragma unroll
-        for (int c = 0; c < S::TI; ++c) acc[t][c] = __builtin_fmaf(qt[j * B + c], w, acc[t][c]);
-      }
-    }
+      for (int c = 0; c < TI; ++c) acc[t][c] = __builtin_fmaf(q[c], w[t], acc[t][c]);
   }
-  const int c_out = kblk * B + h * S::TI;
-  float pm[S::TI];
+  const int c_out = kblk * B + h * TI;
+  float pm[TI];
 #pragma unroll
-  for (int c = 0; c < S::TI; ++c) pm[c] = post_mult ? post_mult[c_out + c] : 1.0f;
+  for (int c = 0; c < TI; ++c) pm[c] = post_mult ? post_mult[c_out + c] : 1.0f;
 #pragma unroll
   for (int t = 0; t < TR; ++t) {
     const int64_t row = row0 + r0 + t;
     if (row < M) {
-      float v[S::TI];
+      float v[TI];
 #pragma unroll
-      for (int c = 0; c < S::TI; ++c) v[c] = post_mult ? acc[t][c] * pm[c] : acc[t][c];
-      if constexpr (S::TI == 4) {
+      for (int c = 0; c < TI; ++c) v[c] = post_mult ? acc[t][c] * pm[c] : acc[t][c];
+      if constexpr (TI == 4) {
         *reinterpret_cast<float4 *>(z + row * K + c_out) = float4{v[0], v[1], v[2], v[3]};
       } else {
 #pragma unroll
-        for (int c = 0; c < S::TI; ++c) z[row * K + c_out + c] = v[c];
+        for (int c = 0; c < TI; ++c) z[row * K + c_out + c] = v[c];
       }
     }
   }
@@ -384,15 +291,10 @@ template <typename Tin, int B, int TR>
 static hipError_t launch_rot_tr(const void *x, int64_t ldx, const int32_t *perm, const float *blocks,
                                 const float *chan_mult, const float *post_mult, int64_t M, int K, float *z,
                                 hipStream_t s) {
-  constexpr size_t lds = rot_lds_bytes<B, TR>();
-  static_assert(lds <= 160 * 1024, "LDS budget");
-  static std::atomic<uint64_t> attr{0};
-  hipError_t e = allow_dynamic_lds(&rot_transform_kernel<Tin, B, TR>, lds, attr);
-  if (e != hipSuccess) return e;
-  constexpr int R = rot_rows<B, TR>();
+  constexpr int R = RotShape<B, TR>::R;
   const int64_t gy = (M + R - 1) / R;
   if (gy > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((rot_transform_kernel<Tin, B, TR>), dim3((unsigned)(K / B), (unsigned)gy), dim3(256), lds, s,
+  hipLaunchKernelGGL((rot_transform_kernel<Tin, B, TR>), dim3((unsigned)(K / B), (unsigned)gy), dim3(256), 0, s,
                      x, ldx, perm, blocks, chan_mult, post_mult, M, K, z);
   return hipGetLastError();
 }
@@ -403,9 +305,10 @@ template <typename Tin, int B>
 static hipError_t launch_rot_b(const void *x, int64_t ldx, const int32_t *perm, const float *blocks,
                                const float *chan_mult, const float *post_mult, int64_t M, int K, float *z,
                                hipStream_t s) {
-  const int64_t wide = (K / B) * ((M + rot_rows<B, 4>() - 1) / rot_rows<B, 4>());
-  return wide >= 256 ? launch_rot_tr<Tin, B, 4>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s)
-                     : launch_rot_tr<Tin, B, 1>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
+  constexpr int R = RotShape<B, 4>::R;
+  return (K / B) * ((M + R - 1) / R) >= 256
+             ? launch_rot_tr<Tin, B, 4>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s)
+             : launch_rot_tr<Tin, B, 1>(x, ldx, perm, blocks, chan_mult, post_mult, M, K, z, s);
 }
 
 template <typename Tin, int B, int RT>
