@@ -4,11 +4,11 @@
 
 Every HIP source is compiled with -ffp-contract=off (the prologue's codes must be
 reproducible bit for bit: no multiply-add may be fused) and with packed-fp32
-instructions disabled.  The GEMM sources keep MFMA accumulators in ordinary VGPRs
-(``-amdgpu-mfma-vgpr-form``): with them in AGPRs the register allocator splits the budget
-in half and spills the GEMM's double-buffered operands into AGPRs.  The k-group GEMM
-(``fq_gemm_kg.hip``) is the exception: its 128 accumulators and two register sets of
-operands need the AGPRs.
+instructions disabled.  ``fq_gemm.hip`` and ``fq_small.hip`` keep MFMA accumulators in
+ordinary VGPRs (``-amdgpu-mfma-vgpr-form``): with them in AGPRs the register allocator
+splits the budget in half and spills their double-buffered operands into AGPRs.  The
+k-group GEMM (``fq_gemm_kg.hip``, 128 accumulators and three register sets of operands) and
+the wide-tile GEMMs (``fq_gemm_wide.hip``) need the AGPRs.
 """
 from __future__ import annotations
 

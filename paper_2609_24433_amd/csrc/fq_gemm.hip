@@ -1346,7 +1346,8 @@ hipError_t launch_gemm(const GemmArgs &g, const GemmPlan &pl, void *ws, hipStrea
   p.partial = pl.splits > 1 ? reinterpret_cast<int32_t *>(ws) : nullptr;
   p.order = pl.order;
   if (pl.kind == 4) {
-    if (g.a_fmt != (g.bits == 4 ? kAF6Major : kAInt8) || g.lda != g.K * g.bits / 8) return hipErrorInvalidValue;
+    if (g.a_fmt != (g.bits == 4 ? kAF6Major : kAInt8) || g.lda != g.K * g.bits / 8 || (g.bits == 4 && g.acc_out))
+      return hipErrorInvalidValue;
     WideParams wp{g.a, g.delta, g.w, g.w_scale, g.bias, g.y, g.ldy, g.acc_out, p.M, p.N, p.K};
     return launch_gemm_wide(wp, g.bits, s, go);
   }

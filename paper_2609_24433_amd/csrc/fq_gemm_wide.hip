@@ -46,14 +46,15 @@ __device__ __forceinline__ void tile_of(int lin, int total, int ntm, int ntn, in
 // A wave's 32 TI x 32 TJ part (rows rw, columns cw of the workgroup's tile) of the output.  Lane
 // l holds column l % 32 and rows 8 (e / 4) + 4 (l / 32) + e % 4 of each 32 x 32 tile; `sums`
 // gives the exact integer sum of (i, j, e).  The wave rescales, stages its bf16 rows in its own
-// part of LDS and stores them in 16-byte chunks.
-template <int TI, int TJ, typename F>
+// part of LDS and stores them in 16-byte chunks.  ACC: raw accumulators on request (the INT8 GEMM
+// entry point; INT4 comes here only from the fused projection, which has none).
+template <int TI, int TJ, bool ACC, typename F>
 __device__ __forceinline__ void write_out(const WideParams &p, F sums, uint8_t *lds, const float *sdelta, int wave,
                                           int rw, int cw, int m0, int n0) {
   constexpr int STRIDE = 32 * TJ * 2 + 16;
   const int lane = threadIdx.x & 63;
   const int u = lane >> 5, cl = lane & 31;
-  if (p.acc_out) {  // raw accumulators for verification
+  if (ACC && p.acc_out) {
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(64 * k8Waves) void gemm_wide8_kernel(WideParams p) 
   wait_vmcnt<0>();
   __syncthreads();  // the ring's trailing loads and reads are over: LDS is reused
   auto sums = [&](int i, int j, int e) -> int { return acc[i][j][e]; };
-  write_out<TI, TJ>(p, sums, lds, sdelta, wave, wave * 64, 0, m0, n0);
+  write_out<TI, TJ, true>(p, sums, lds, sdelta, wave, wave * 64, 0, m0, n0);
 }
 
 // ---------------- INT4 on the FP6 matrix cores ----------------
@@ -391,7 +392,7 @@ __global__ __launch_bounds__(64 * k4Waves) void gemm_wide4_kernel(WideParams p) 
   auto sums = [&](int, int j, int e) -> int {
     return (int)(acc[j][e] * 64.0f) + (cc[j] - 8 * rsum[wave * 32 + 8 * (e >> 2) + 4 * u + (e & 3)]);
   };
-  write_out<1, TJ>(p, sums, lds, sdelta, wave, wave * 32, 0, m0, n0);
+  write_out<1, TJ, false>(p, sums, lds, sdelta, wave, wave * 32, 0, m0, n0);
 }
 
 }  // namespace
