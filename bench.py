@@ -565,16 +565,17 @@ def summarize_trace(path, manifest_path, out_path=POINTS_TRACE_FILE):
 # --------------------------------------------------------------------------- counter summaries
 
 def counter_rows(run_dir):
-    """(dispatch id, kernel, grid threads, counter, value) rows of one rocprofv3 --pmc run
-    (csv output under run_dir)."""
+    """(dispatch id, kernel, grid threads, counter, value, duration in ns or None) rows of one rocprofv3
+    --pmc run (csv output under run_dir)."""
     import csv
     import glob
     rows = []
     for path in glob.glob(os.path.join(run_dir, "**", "*counter_collection.csv"), recursive=True):
         with open(path) as f:
             for r in csv.DictReader(f):
+                ns = float(r["End_Timestamp"]) - float(r["Start_Timestamp"]) if r.get("End_Timestamp") else None
                 rows.append((int(r["Dispatch_Id"]), r["Kernel_Name"], int(r["Grid_Size"]), r["Counter_Name"],
-                             float(r["Counter_Value"])))
+                             float(r["Counter_Value"]), ns))
     if not rows:
         raise SystemExit(f"no counter rows under {run_dir}")
     return rows
@@ -583,9 +584,11 @@ def counter_rows(run_dir):
 def counter_means(run_dir, min_dispatches):
     """(kernel, grid) -> {"dispatches": n, counter: mean per dispatch} over the kernels
     dispatched at least min_dispatches times (the measured calls; set-up kernels such as
-    the weight rounding and packing run once)."""
+    the weight rounding and packing run once).  DURATION_NS is the dispatch's own time."""
     per = {}
-    for disp, name, grid, ctr, val in counter_rows(run_dir):
+    for disp, name, grid, ctr, val, ns in counter_rows(run_dir):
+        if ns is not None:
+            per.setdefault((name, grid), {}).setdefault("DURATION_NS", {})[disp] = ns
         d = per.setdefault((name, grid), {})
         d.setdefault(ctr, {})[disp] = d.get(ctr, {}).get(disp, 0.0) + val
     out = {}
@@ -745,6 +748,9 @@ def summarize_counters(d, points, out_path=os.path.join(PROFILES, "gemm_counters
                    "mfma_busy_cycles_per_mfma": round(v.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0) / mfma, 1) if mfma else None,
                    # GRBM_GUI_ACTIVE summed over the 8 XCDs: SIMD cycles = 1024 x gui / 8
                    "mfma_utilisation": round(v.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0) / (1024 * gui / 8), 3) if gui else None,
+                   # XCD cycles over the dispatch's time (GRBM_GUI_ACTIVE comes with the sq2 set)
+                   "us_under_counters": round(v["DURATION_NS"] / 1e3, 1) if "DURATION_NS" in v else None,
+                   "clock_ghz": round(gui / 8 / v["DURATION_NS"], 2) if gui and v.get("DURATION_NS") else None,
                    "lds_instr_per_mfma": round(v.get("SQ_INSTS_LDS", 0.0) / mfma, 3) if mfma else None,
                    "lds_bank_conflicts": int(v.get("SQ_LDS_BANK_CONFLICT", 0.0)),
                    "wait_per_wave_cycles": round(v.get("SQ_WAIT_INST_ANY", 0.0) / v["SQ_WAVE_CYCLES"], 3)
@@ -774,19 +780,20 @@ def summarize_counters(d, points, out_path=os.path.join(PROFILES, "gemm_counters
               f"HBM bytes: FETCH_SIZE and WRITE_SIZE divided by what they read for the copy calibration: factors "
               f"{ff:.4f} and {fw:.4f}.  MFMA utilisation = SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x GRBM_GUI_ACTIVE / 8), "
               "GRBM_GUI_ACTIVE summed over the 8 XCDs (it includes the profiler's per-dispatch overhead, so it reads "
-              "a little below the timed points).  VALU / MFMA counts the other vector instructions per MFMA "
+              "a little below the timed points).  Clock = GRBM_GUI_ACTIVE / 8 over the dispatch's time in that run "
+              "(a little high for the same reason, most for short kernels).  VALU / MFMA counts the other vector instructions per MFMA "
               "(SQ_INSTS_VALU includes the MFMAs).  Per-dispatch means over the point's calls (one per weight "
               f"copy).  Sources SHA-256 {res['sources_sha256'][:16]}.", "",
               "| point | kernel | grid (threads) | dispatches | HBM read MB | HBM write MB | algorithmic MB | L2 hit rate "
-              "| waves | MFMA | VALU / MFMA | MFMA busy cycles / MFMA | MFMA utilisation | LDS instr / MFMA | "
+              "| waves | MFMA | VALU / MFMA | MFMA busy cycles / MFMA | MFMA utilisation | us | clock GHz | LDS instr / MFMA | "
               "LDS bank conflicts | wait / wave cycles | VALU active / wave cycles |",
-              "|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
+              "|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
     for pt, pr in res["points"].items():
         for k in pr["kernels"]:
             lines.append(f"| {pt} | `{k['kernel']}` | {k['grid_threads']} | {k['dispatches']} | {k['hbm_read_mb']} | "
                          f"{k['hbm_write_mb']} | {pr['algorithmic_mb']} | {k['l2_hit_rate']} | {k['waves']} | "
                          f"{k['mfma']} | {k['valu_per_mfma']} | {k['mfma_busy_cycles_per_mfma']} | "
-                         f"{k['mfma_utilisation']} | {k['lds_instr_per_mfma']} | {k['lds_bank_conflicts']} | "
+                         f"{k['mfma_utilisation']} | {k['us_under_counters']} | {k['clock_ghz']} | {k['lds_instr_per_mfma']} | {k['lds_bank_conflicts']} | "
                          f"{k['wait_per_wave_cycles']} | {k['valu_active_per_wave_cycles']} |")
     with open(out_path.replace(".json", ".md"), "w") as fo:
         fo.write("\n".join(lines) + "\n")

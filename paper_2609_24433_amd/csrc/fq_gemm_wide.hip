@@ -6,7 +6,8 @@
 // operations per multiply.  These tiles move 3/4 of the bytes, W4A4 multiplies on the FP6 matrix
 // cores (fq_f6.hpp: twice the INT8 rate, and 2.5x fewer widening operations per product), and 32 x
 // 32 instructions leave twice the issue slots between multiplies.  At full occupancy power bounds
-// both: the clock falls from 2.3 to 1.8 GHz with the matrix pipe 63% busy (W8A8, uniform codes).
+// W8A8: at M = 4096, K 16384 -> N 2048 the clock falls to 1.8 GHz with the matrix pipe 61% busy.
+// W4A4 runs at 2.2 GHz there with the pipe 48% busy (profiles/gemm_counters.md).
 #include "fq_device.hpp"
 #include "fq_f6.hpp"
 #include "fq_launch.hpp"

@@ -336,8 +336,9 @@ constexpr int kNb = 64;  // Cholesky / inverse block
 // pivot by two Newton steps on the hardware estimate, exact at 1), then the waves update the
 // rest; the inverse follows from the 16-wide diagonal blocks' inverses (16-wide products on the
 // matrix instruction).  a: the block (lower part), becomes L with zeros above; x: becomes L^-1.
-// One wave's chain of 64 pivots bounds it (about 0.25 us each); the former wave-per-block
-// factor and the row-parallel solves with fp64 divisions took 83 us a block.
+// One wave's chain of 64 pivots bounds it (about 0.25 us each; the pivot row's values in scalar
+// register pairs are more than there are, so the compiler keeps about 200 of them in vector lanes);
+// the former wave-per-block factor and the row-parallel solves with fp64 divisions took 83 us a block.
 constexpr int kLd = kNb + 1;
 __device__ __forceinline__ double lane_value(double v, int lane) {
   const uint64_t b = __builtin_bit_cast(uint64_t, v);

@@ -138,8 +138,9 @@ __device__ __forceinline__ float4 transpose_quarters(float4 f) {
 // A lane ends with 4 consecutive channels of one row: one 16-byte store.  The next tile's gather
 // is in flight under the products.  M = 816, K = 2048, b = 128: 14.4 us, against 17.5 for the
 // register-tiled fma chains this replaced (bound by their LDS reads of both operands); M = 16 6.2
-// against 7.4; b = 16 9.0 against 13.5.  What is left is the gather (9 us by itself with b = 16:
-// every 2-byte input is a lane address of its own), then the products (3.4 us at the fp32 rate).
+// against 7.4; b = 16 9.0 against 13.5.  What is left is mostly the gather (every 2-byte input is a lane
+// address of its own: with b = 16, an eighth of the products and of the matrix, the kernel still takes
+// 9 us), then the products (3.4 us at the fp32 rate).
 constexpr int kRotPitch = 132;
 
 template <typename Tin, int B, int RT>
