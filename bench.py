@@ -780,8 +780,9 @@ def summarize_counters(d, points, out_path=os.path.join(PROFILES, "gemm_counters
               f"HBM bytes: FETCH_SIZE and WRITE_SIZE divided by what they read for the copy calibration: factors "
               f"{ff:.4f} and {fw:.4f}.  MFMA utilisation = SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x GRBM_GUI_ACTIVE / 8), "
               "GRBM_GUI_ACTIVE summed over the 8 XCDs (it includes the profiler's per-dispatch overhead, so it reads "
-              "a little below the timed points).  Clock = GRBM_GUI_ACTIVE / 8 over the dispatch's time in that run "
-              "(a little high for the same reason, most for short kernels).  VALU / MFMA counts the other vector instructions per MFMA "
+              "a little below the timed points).  Clock = GRBM_GUI_ACTIVE / 8 over the dispatch's time in that run, "
+              "an upper bound: the same overhead adds some 15 000 cycles, a tenth of a 75 us kernel's and more than "
+              "half of a 10 us one's.  VALU / MFMA counts the other vector instructions per MFMA "
               "(SQ_INSTS_VALU includes the MFMAs).  Per-dispatch means over the point's calls (one per weight "
               f"copy).  Sources SHA-256 {res['sources_sha256'][:16]}.", "",
               "| point | kernel | grid (threads) | dispatches | HBM read MB | HBM write MB | algorithmic MB | L2 hit rate "

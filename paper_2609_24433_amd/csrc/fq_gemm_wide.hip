@@ -5,9 +5,9 @@
 // unit from L2 at W8A8's rate (a compute unit takes 52-58) and, for W4A4, issues 3 widening
 // operations per multiply.  These tiles move 3/4 of the bytes, W4A4 multiplies on the FP6 matrix
 // cores (fq_f6.hpp: twice the INT8 rate, and 2.5x fewer widening operations per product), and 32 x
-// 32 instructions leave twice the issue slots between multiplies.  At full occupancy power bounds
-// W8A8: at M = 4096, K 16384 -> N 2048 the clock falls to 1.8 GHz with the matrix pipe 61% busy.
-// W4A4 runs at 2.2 GHz there with the pipe 48% busy (profiles/gemm_counters.md).
+// 32 instructions leave twice the issue slots between multiplies.  At full occupancy power
+// bounds W8A8: at M = 4096, K 16384 -> N 2048 the clock is at most 1.8 GHz with the matrix pipe 60%
+// busy.  W4A4 runs there at up to 2.2 GHz with the pipe 48% busy (profiles/gemm_counters.md).
 #include "fq_device.hpp"
 #include "fq_f6.hpp"
 #include "fq_launch.hpp"
