@@ -1000,11 +1000,13 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // rounds.  A round takes it less time, by more the longer K is, since its tiles start and end more
 // slowly.  Fused calls, cold weights, us wide / LDS ring or the ratio:
 //   as many rounds: W4A4 K 16384 -> N 2048 M = 4096 102 / 139, K 2048 -> N 16384 M = 816 33 / 40, one
-//   round K = 384 0.91 to 1.0 and K = 256 1.03 to 1.05, more rounds K = 1024 0.89 to 1.0, K = 768 and
-//   896 0.89 to 0.99 with the last round filled and 0.99 to 1.08 else; W8A8 K 2048 -> N 16384 M = 816
-//   46 / 58, one round K = 128 0.86 to 0.94, three and more K = 128 to 384 0.83 to 1.03, two K = 512
-//   0.77 to 1.02, K = 128 to 384 0.82 to 1.06 filled and 0.96 to 1.07 else;
-//   up to 6/5 as many: W4A4 K = 1408 0.96 to 0.97 and 1280 1.01, W8A8 K = 256 0.86 to 0.99;
+//   round K = 384 0.91 to 1.0 and K = 256 1.03 to 1.05, more rounds K = 1024 0.89 to 1.0, K = 640 to
+//   896 0.89 to 1.0 with at least 60% of the last round filled and 0.98 to 1.08 else; W8A8 K 2048 ->
+//   N 16384 M = 816 46 / 58, one round K = 128 0.86 to 0.94, three and more K = 128 to 384 0.83 to
+//   1.05, two K = 512 0.77 to 1.02, K = 128 to 384 0.82 to 1.04 with 45% of the second filled and
+//   0.96 to 1.07 else;
+//   up to 6/5 as many: W4A4 K = 1408 0.96 to 0.97 and 1280 1.01, W8A8 K = 128 0.90 to 0.93, K = 256 0.86
+//   to 0.99;
 //   up to 4/3 as many: W4A4 K = 1792 0.98 to 0.99 and 1408 1.04, W8A8 K = 512 0.87 to 1.02 and 384
 //   0.94 to 1.05;
 //   up to 3/2 as many: W4A4 K = 3072 0.99 and 2304 1.01 to 1.06, W8A8 K = 3712 0.96 and 2944 0.93 to 1.04;
@@ -1015,12 +1017,12 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // -> N 2048 M = 816: 42 + 6.7 us of epilogue against 40 + 5.2 on heavy-tailed tokens).
 static bool wide_pays(int64_t t128, int64_t t256, int ktot, int bits) {
   const int64_t ring = (t128 + 511) / 512, wide = (t256 + 255) / 256;
-  const bool filled = wide * 256 - t256 <= 102;  // at least 60% of the last round
+  const int64_t idle = wide * 256 - t256;  // compute units without a tile in the last round
   if (wide <= ring) {
-    if (bits == 8) return ktot >= 4 || wide != 2 || filled;
-    return ktot >= (wide == 1 ? 3 : filled ? 6 : 8);
+    if (bits == 8) return ktot >= 4 || wide != 2 || idle <= 140;
+    return ktot >= (wide == 1 ? 3 : idle <= 102 ? 5 : 8);
   }
-  if (5 * wide <= 6 * ring) return ktot >= (bits == 4 ? 11 : 2);
+  if (5 * wide <= 6 * ring) return bits == 8 || ktot >= 11;
   if (3 * wide <= 4 * ring) return ktot >= (bits == 4 ? 14 : 4);
   return 2 * wide <= 3 * ring && ktot >= (bits == 4 ? 24 : 28);
 }

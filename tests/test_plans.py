@@ -34,12 +34,13 @@ def kind(M, K, N, bits, fused=True):
     (383, 2944, 32896, 4, LDS_RING), (383, 3072, 32896, 4, WIDE), (383, 3456, 32896, 8, LDS_RING),
     (383, 3584, 32896, 8, WIDE), (831, 1664, 25600, 4, LDS_RING), (831, 1792, 25600, 4, WIDE),
     (831, 384, 25600, 8, LDS_RING), (831, 512, 25600, 8, WIDE),
-    (1647, 1280, 24320, 4, LDS_RING), (1647, 1408, 24320, 4, WIDE), (1647, 256, 24320, 8, WIDE),
+    (1647, 1280, 24320, 4, LDS_RING), (1647, 1408, 24320, 4, WIDE), (1647, 128, 24320, 8, WIDE),
     # short K: one round, two, three
     (2048, 256, 4096, 4, LDS_RING), (2048, 384, 4096, 4, WIDE), (2048, 128, 4096, 8, WIDE),
     (2277, 896, 4992, 4, LDS_RING), (2277, 1024, 4992, 4, WIDE),
     (2277, 384, 4992, 8, LDS_RING), (2277, 512, 4992, 8, WIDE),
-    (3041, 640, 5168, 4, LDS_RING), (3041, 768, 5168, 4, WIDE), (3041, 128, 5168, 8, WIDE),
+    (3041, 512, 5168, 4, LDS_RING), (3041, 640, 5168, 4, WIDE), (3041, 128, 5168, 8, WIDE),
+    (1280, 384, 9872, 8, WIDE), (1280, 384, 9344, 8, LDS_RING),
     (3078, 128, 7360, 8, WIDE),
     # one 128 x 128 tile per compute unit
     (2048, 2048, 2048, 8, LDS_RING), (2048, 2048, 2064, 8, WIDE),
