@@ -7,7 +7,7 @@
 // cores (fq_f6.hpp: twice the INT8 rate, and 2.5x fewer widening operations per product), and 32 x
 // 32 instructions leave twice the issue slots between multiplies.  At full occupancy power
 // bounds W8A8: at M = 4096, K 16384 -> N 2048 the clock is at most 1.8 GHz with the matrix pipe 60%
-// busy.  W4A4 runs there at up to 2.2 GHz with the pipe 48% busy (profiles/gemm_counters.md).
+// busy.  W4A4 runs there at up to 2.2 GHz with the pipe 48% busy (counters under profiles/).
 #include "fq_device.hpp"
 #include "fq_f6.hpp"
 #include "fq_launch.hpp"
