@@ -204,11 +204,12 @@ fq_status gemm_entry(int bits, const void *a_codes, const float *delta, const vo
 
 // fq_linear workspace: none when one fused kernel runs the projection (few tokens, K up
 // to 4096); otherwise [codes (4-bit for W4A4, int8 for W8A8)][delta][split-K partials]
-size_t linear_ws_bytes(int64_t M, int64_t N, int64_t K, int bits) {
+// `scratch`: what the caller has for the partials (plan_linear).
+size_t linear_ws_bytes(int64_t M, int64_t N, int64_t K, int bits, size_t scratch = SIZE_MAX) {
   if (M <= 0 || N <= 0 || K < 128 || (bits != 4 && bits != 8)) return 0;
   if (fq::plan_small(M, N, K, bits).ok) return 0;
   return align256((size_t)M * (size_t)K * (size_t)bits / 8) + align256((size_t)M * 4) +
-         fq::gemm_plan_workspace(fq::plan_gemm(M, N, K, bits, true));
+         fq::gemm_plan_workspace(fq::plan_linear(M, N, K, bits, scratch));
 }
 
 int log2_pow2(int b) {
@@ -232,9 +233,11 @@ fq_status linear_common(const void *x_bf16, int64_t ldx, const float *smooth_inv
   if (M == 0 || N == 0) return ok();
   const size_t codes_bytes = align256((size_t)M * (size_t)K * (size_t)bits / 8);
   const size_t delta_bytes = align256((size_t)M * 4);
-  const size_t need = linear_ws_bytes(M, N, K, bits);
+  const size_t fixed = codes_bytes + delta_bytes;
+  const size_t need = linear_ws_bytes(M, N, K, bits, ws && ws_bytes > fixed ? ws_bytes - fixed : 0);
   if (need > 0 && (!ws || ws_bytes < need))
-    return fail(FQ_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, ws ? ws_bytes : (size_t)0);
+    return fail(FQ_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", linear_ws_bytes(M, N, K, bits),
+                ws ? ws_bytes : (size_t)0);
   if (need > 0 && !aligned16(ws)) return fail(FQ_ERR_ALIGN, "workspace must be 16-byte aligned");
   if (outputs_alias({span(y_bf16, rows_span(M, ldy * 2, N * 2)), span(need ? ws : nullptr, need)},
                     {span(x_bf16, rows_span(M, ldx * 2, K * 2)), span(smooth_inv, smooth_inv ? (size_t)K * 4 : 0),
@@ -268,10 +271,10 @@ fq_status linear_common(const void *x_bf16, int64_t ldx, const float *smooth_inv
   uint8_t *codes = static_cast<uint8_t *>(ws);
   float *delta = reinterpret_cast<float *>(codes + codes_bytes);
   void *gws = codes + codes_bytes + delta_bytes;
-  const size_t gws_bytes = ws_bytes - codes_bytes - delta_bytes;
+  const size_t gws_bytes = ws_bytes - fixed;
   // W4A4 codes between the two kernels take 4 bits, W8A8 codes 8, canonical or, for the
   // kernels that read them so, k major.
-  const fq::GemmPlan pl = fq::plan_gemm(M, N, K, bits, true);
+  const fq::GemmPlan pl = fq::plan_linear(M, N, K, bits, gws_bytes);
   const bool nibble = bits == 4, major = fq::plan_major_codes(pl, bits);
   const int fmt = nibble ? (major ? fq::kOutF6Major : fq::kOutNibble) : fq::kOutInt8;
   const int afmt = nibble ? (major ? fq::kAF6Major : fq::kANibble) : fq::kAInt8;
@@ -540,7 +543,8 @@ fq_status fq_linear_static(const void *x_bf16, int64_t ldx, const float *smooth_
   if (s != FQ_OK) return s;
   if ((s = check_gemm(x_bf16, w_scale, w_packed, w_scale, bias, y_bf16, ldy, nullptr, M, N, K)) != FQ_OK) return s;
   if (M == 0 || N == 0) return ok();
-  const size_t need = linear_ws_bytes(M, N, K, bits);
+  const size_t fixed = align256((size_t)M * (size_t)K * (size_t)bits / 8) + align256((size_t)M * 4);
+  const size_t need = linear_ws_bytes(M, N, K, bits, kStaticScratchBytes > fixed ? kStaticScratchBytes - fixed : 0);
   if (need > kStaticScratchBytes)
     return fail(FQ_ERR_WORKSPACE, "this shape needs %zu bytes of scratch; fq_linear_static holds %zu", need,
                 kStaticScratchBytes);

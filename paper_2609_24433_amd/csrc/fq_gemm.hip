@@ -1037,14 +1037,19 @@ static bool wide_pays(int64_t t128, int64_t t256, int ktot, int bits) {
 //   64 tiles of 128 x 128 (0.91 to 1.26 there), but not above: 65 to 128 0.75 to 0.96, 129 to 199 0.82
 //   to 0.97, 200 to 256 0.85 to 0.97 (K 8192 to 9088 0.97 to 1.10).  K 16384 -> N 2048: M = 816 39.8 /
 //   53.0, M = 1600 69.4 / 76.6.
-// With more than 46 MB of codes the small grids stay here all the same: up to 17 MB of partial sums
-// beside them would not fit the 64 MiB of fq_linear_static (M = 8000, K 16384 -> N 128 96 / 83).
-static bool kgroup_pays(int64_t M, int64_t N, int64_t K, int64_t t128, int64_t tkg) {
-  const int ktot = (int)(K / kTileK);
+static bool kgroup_pays(int64_t N, int ktot, int64_t t128, int64_t tkg) {
   if (ktot < 32 || t128 > 256) return false;
   if (ktot < 64) return tkg <= (N > 512 ? 256 : 200);
-  if (t128 <= 64) return M * K > (int64_t(11) << 23) && tkg >= (ktot < 128 ? 48 : 96);
-  return ktot >= 72 || t128 < 200;
+  return t128 > 64 && (ktot >= 72 || t128 < 200);
+}
+
+static GemmPlan kgroup_plan(int64_t tkg, int ktot) {
+  GemmPlan pl{};
+  pl.kind = 3;
+  pl.tiles = tkg;
+  pl.splits = 1;
+  pl.ksteps = ktot;
+  return pl;
 }
 
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused) {
@@ -1130,23 +1135,13 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused) {
       pl.ksteps = ktot;
       return pl;
     }
-    if (off32 && bits == 4 && fused && kgroup_pays(M, N, K, t128, tkg)) {
-      pl.kind = 3;
-      pl.tiles = tkg;
-      pl.splits = 1;
-      pl.ksteps = ktot;
-      return pl;
-    }
+    if (off32 && bits == 4 && fused && kgroup_pays(N, ktot, t128, tkg)) return kgroup_plan(tkg, ktot);
     if (off32 && bits == 4 && !fused && ktot >= 64 && t128 < 200 && tkg >= 160) {
       // Canonical codes: kind 3 still pays for their conversion (a kernel of its own) where
       // 128 x 128 tiles would need a split K (K 16384 -> N 2048, M = 816: 35 us with the
       // conversion against 43 us on one GPU).  Short K and grids of fewer than 160 tiles stay on
       // the LDS-ring kernel below.
-      pl.kind = 3;
-      pl.tiles = tkg;
-      pl.splits = 1;
-      pl.ksteps = ktot;
-      return pl;
+      return kgroup_plan(tkg, ktot);
     }
     pl.kind = 1;
     // K slices: split a grid of fewer than 200 tiles while each slice keeps >= 32 steps
@@ -1181,6 +1176,18 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused) {
   }
   pl.partial_bytes = pl.splits > 1 ? align256((size_t)pl.splits * M * N * 4) : 0;
   return pl;
+}
+
+GemmPlan plan_linear(int64_t M, int64_t N, int64_t K, int bits, size_t scratch) {
+  const GemmPlan pl = plan_gemm(M, N, K, bits, true);
+  if (pl.partial_bytes <= scratch || pl.kind != 1 || bits != 4) return pl;
+  // Small grids at long K whose split needs more scratch than there is: the k groups need none
+  // (M = 8000, K 16384 -> N 128 97 us against 84).  From 48 tiles (96 from K = 16384) on, what a
+  // workspace without partial sums, that of a larger M for one, has served.
+  const int ktot = (int)(K / kTileK);
+  const int64_t tkg = ((M + 127) / 128) * ((N + 63) / 64);
+  const bool off32 = M * K / 2 < (int64_t(1) << 31) && N * K / 2 < (int64_t(1) << 31);
+  return off32 && ktot >= 64 && tkg >= (ktot < 128 ? 48 : 96) ? kgroup_plan(tkg, ktot) : pl;
 }
 
 size_t gemm_plan_workspace(const GemmPlan &pl) { return pl.partial_bytes; }

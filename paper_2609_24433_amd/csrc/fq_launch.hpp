@@ -84,6 +84,8 @@ struct GemmPlan {
 // the plan wants them so (plan_major_codes), which opens plan kind 4 to INT4 and widens kind 3's
 // range.
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, bool fused = false);
+// plan_gemm for the fused projection with `scratch` bytes for the GEMM: one that fits where there is one.
+GemmPlan plan_linear(int64_t M, int64_t N, int64_t K, int bits, size_t scratch);
 inline bool plan_major_codes(const GemmPlan &pl, int bits) { return bits == 4 && (pl.kind == 3 || pl.kind == 4); }
 // scratch of the GEMM itself (split-K partials); a kind-3 plan fed canonical codes also
 // needs gemm_plan_relayout_bytes for their k-major copy

@@ -91,3 +91,27 @@ def test_long_sums_to_the_last_unit(M, N):
     want = (step.double().to(DEV) @ w.double().to(DEV).t().contiguous()).long()
     assert int(want.abs().max()) < 256 and int(sum0.max()) > 1_000_000
     assert torch.equal(y.long(), want)
+
+
+@pytest.mark.parametrize("M,K,N", [(384, 16384, 2048), (358, 9088, 1024), (1664, 24576, 512)])
+def test_a_workspace_without_partial_sums(M, K, N):
+    """Grids whose split K wants partial sums, with a workspace that holds the codes and scales only (that
+    of a shape on the k groups): served without them, the same output; less is refused."""
+    from paper_2609_24433_amd import fq
+    flush(f"no partial sums M={M} K={K} N={N}")
+    x = synth.activations(M, K, seed=M, outlier_frac=0.01, outlier_scale=30.0).to(DEV)
+    wc, sw = fq.quantize_weights(torch.from_numpy(synth.weights(N, K, seed=N)).to(DEV), 128, 4)
+    wp = fq.pack_weights(wc, 4)
+    least = (M * K // 2 + 255) // 256 * 256 + (M * 4 + 255) // 256 * 256
+    full = fq.linear_workspace_bytes(M, N, K, 4)
+    assert full > least
+    ys = []
+    for size in (full, full - 256, least):
+        room = torch.full((size + 4096,), 7, dtype=torch.uint8, device=DEV)
+        ys.append(fq.linear(x, wp, sw, N, 128, 4, ws=room[:size]))
+        torch.cuda.synchronize()
+        assert bool((room[size:] == 7).all())  # nothing past the workspace
+    assert torch.equal(ys[0], ys[1]) and torch.equal(ys[0], ys[2])
+    with pytest.raises(fq.FQError) as e:
+        fq.linear(x, wp, sw, N, 128, 4, ws=torch.empty((least - 256,), dtype=torch.uint8, device=DEV))
+    assert e.value.status == 5 and str(full) in str(e.value)
